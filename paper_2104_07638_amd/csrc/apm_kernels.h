@@ -115,6 +115,11 @@ struct LaunchXor {
 // Elements of top-level workspace per matrix with n blocks (0: none needed).
 int64_t xor_ws_elems(int n, int mode);
 hipError_t xor_launch(const LaunchXor& L, hipStream_t st);
+// The register kernels (4 blocks and more, no workspace).
+hipError_t xor_row_launch_r64(const LaunchXor& L, hipStream_t st);
+hipError_t xor_row_launch_c128(const LaunchXor& L, hipStream_t st);
+hipError_t xnor_row_launch_r64(const LaunchXor& L, hipStream_t st);
+hipError_t xnor_row_launch_c128(const LaunchXor& L, hipStream_t st);
 
 // Leading principal minors: [batch][n] of [batch][n][n] (dtype R64 or C128, n <= 32).
 hipError_t lead_launch(int dtype, const void* A, void* out, int32_t* info, int32_t batch, int n, hipStream_t st);

@@ -54,6 +54,7 @@ namespace {
 #endif
 constexpr int kXQ = APM_XOR_Q;   // levels expanded breadth first in LDS (XOR, XNOR)
 constexpr int kXQ3 = 4;      // the same for the ternary NAND tree
+constexpr int kRowMin = 4;   // XOR and XNOR from here on: xor_row.h
 // modes: the XOR, XNOR and NAND cases of Sec. III
 constexpr int kXor = 0, kXnor = 1, kNand = 2;
 __host__ __device__ constexpr int xq(int mode) { return mode == kNand ? kXQ3 : kXQ; }
@@ -820,6 +821,10 @@ int64_t xor_ws_elems(int n, int mode)
 
 hipError_t xor_launch(const LaunchXor& L, hipStream_t st)
 {
+    if (L.mode != kNand && L.n >= kRowMin) {
+        if (L.mode == kXor) return L.dtype == 0 ? xor_row_launch_r64(L, st) : xor_row_launch_c128(L, st);
+        return L.dtype == 0 ? xnor_row_launch_r64(L, st) : xnor_row_launch_c128(L, st);
+    }
     if (L.dtype == 0) return xor_launch_n<FR64, 1>(L, st);
     if (L.dtype == 2) return xor_launch_n<FC128, 1>(L, st);
     return hipErrorInvalidValue;
