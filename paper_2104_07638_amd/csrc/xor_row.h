@@ -27,6 +27,7 @@
 
 #include "apm_device.h"
 #include "apm_kernels.h"
+#include "row_fma.h"
 
 namespace apm {
 namespace xrow {
@@ -34,6 +35,7 @@ namespace xrow {
 constexpr int kXor = 0, kXnor = 1;
 constexpr int kParents = 32;        // order-8 nodes in LDS at a time
 constexpr int kPS = 65;             // their stride in elements
+constexpr int kSlots = 16;
 
 __host__ __device__ constexpr int top_levels(int N) { return N > 8 ? N - 8 : 0; }
 // order-8 nodes of a unit per lane phase, and lane phases per unit
@@ -43,15 +45,24 @@ __host__ __device__ constexpr int halves(int N) { return N >= 8 ? 2 : 1; }
 template <class F>
 struct Lds {
     typename F::E node[kParents * kPS];
-    typename F::E mn[kParents];     // their minors
+    typename F::E mn[4 * kSlots];   // minors of the row phase, kSlots a unit (keep())
+    typename F::E dump[64 + kSlots];
 };
 
-// c - col * w with col = lane P's value of column entries src
+// a - c w with c = lane P's value of src
 template <class F, int P>
 __device__ __forceinline__ typename F::E row_upd(typename F::E a, typename F::E src, typename F::E w)
 {
     return F::upd(a, row_bcast<P>(src), w);
 }
+
+// v where m is all ones, zero where m is zero (no branch around the load of v)
+__device__ __forceinline__ double keep_if(int m, double v)
+{
+    return __hiloint2double(__double2hiint(v) & m, __double2loint(v) & m);
+}
+__device__ __forceinline__ cd keep_if(int m, cd v) { return {keep_if(m, v.x), keep_if(m, v.y)}; }
+__device__ __forceinline__ double unit_if(bool c) { return __hiloint2double(c ? 0x3FF00000 : 0, 0); }
 
 template <class F, int N, int MODE>
 struct Unit {
@@ -59,25 +70,18 @@ struct Unit {
     static constexpr int T = top_levels(N);
     static constexpr int R0 = 2 * (N - T);
     static constexpr int NPR = parents(N);
-    static constexpr int D8 = N - 4;             // depth of the order-8 nodes
+    static constexpr int LV8 = N >= 7 ? 3 : N - 4;   // row-phase levels down to order 8
+    static constexpr int kLast = LV8 ? (1 << LV8) - 2 : 0;   // slot of the first order-8 node's minor
 
     Lds<F>& sh;
     E* ob;            // this row's matrix's output
     int path;         // its choices of the top levels
     int l16;          // lane in the row
-    bool wr;          // the lane that writes the row's minors
+    bool valid;       // whether there is such a unit
+    bool wr;          // the lane that writes the top levels' minors
     double chk = 0.0;
 
     __device__ Unit(Lds<F>& s) : sh(s) {}
-
-    // a minor of depth d (path p below the root)
-    __device__ __forceinline__ void record(int d, int p, E mk)
-    {
-        if constexpr (MODE == kXor) {
-            if (wr) ob[(int64_t(1) << d) - 2 + p] = mk;
-        }
-        chk += F::fincheck(mk);
-    }
 
     // ---------------------------------------------------------------- top phase
     // The depth-T node of the path: M[i] = row i of its lane's column; mk = its minor.
@@ -94,26 +98,78 @@ struct Unit {
             const int kc = 2 * (N - 1 - t) + ((path >> (T - 1 - t)) & 1);
             E w0[T], w1[T];
             top_xor_pivots<0>(A0, kc, w0, w1, mk);
+            // the undecided rows' multipliers with a row per lane: the kept columns eliminated
+            // for all 16 rows at once
+            E c[T];
 #pragma unroll
-            for (int i = 0; i < R0; ++i) {
-                E a0 = A0[i * w + l16], a1 = A0[i * w + kc];
-                apply_xor<0, T>(a0, a1, w0, w1);
-                M[i] = a0;
-            }
+            for (int k = 0; k < T; ++k) c[k] = A0[l16 * w + 2 * (N - 1 - k) + ((path >> (T - 1 - k)) & 1)];
+#pragma unroll
+            for (int i = 0; i < R0; ++i) M[i] = A0[i * w + l16];
+            multipliers<0, 1>(c, w1);
+#pragma unroll
+            for (int k = 0; k < T; ++k) sub_rows<0>(M, c[k], w0[k]);
         } else {
             // lane 2 t + r's kept column: column r of block N - 1 - t (zero if left out)
             const int t = l16 < 2 * T ? l16 >> 1 : T - 1;
             const int kc = 2 * (N - 1 - t) + (l16 & 1);
-            const bool kept = (path >> (T - 1 - t)) & 1;
+            const int kept = -((path >> (T - 1 - t)) & 1);   // as a bit mask
             E wa0[T], wa1[T], wb0[T], wb1[T];
             top_xnor_pivots<0>(A0, kc, kept, wa0, wa1, wb0, wb1, mk);
+            __builtin_amdgcn_sched_barrier(0);   // the rows are loaded once the pivots' registers are free
+            E ca[T], cb[T];
 #pragma unroll
-            for (int i = 0; i < R0; ++i) {
-                E a0 = A0[i * w + l16], a1 = A0[i * w + kc];
-                if (!kept) a1 = F::zero();
-                apply_xnor<0, T>(a0, a1, wa0, wa1, wb0, wb1);
-                M[i] = a0;
+            for (int k = 0; k < T; ++k) {
+                const E* p = A0 + l16 * w + 2 * (N - 1 - k);
+                const int in = -((path >> (T - 1 - k)) & 1);
+                ca[k] = keep_if(in, p[0]);
+                cb[k] = keep_if(in, p[1]);
             }
+            multipliers2<0, 1>(ca, cb, wa1, wb1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < R0; ++i) M[i] = A0[i * w + l16];
+#pragma unroll
+            for (int k = 0; k < T; ++k) {
+                sub_rows<0>(M, ca[k], wa0[k]);
+                sub_rows<0>(M, cb[k], wb0[k]);
+            }
+        }
+    }
+
+    // c[k2] -= c[K] (entry k2 of the scaled pivot row K), K < k2
+    template <int K, int K2>
+    __device__ __forceinline__ void multipliers(E (&c)[T], const E (&w1)[T])
+    {
+        if constexpr (K2 < T) {
+            c[K2] = F::upd(c[K2], c[K], row_bcast<K2>(w1[K]));
+            multipliers<K, K2 + 1>(c, w1);
+        } else if constexpr (K + 2 < T) {
+            multipliers<K + 1, K + 2>(c, w1);
+        }
+    }
+
+    // the same for pivot blocks (two multipliers a block)
+    template <int K, int K2>
+    __device__ __forceinline__ void multipliers2(E (&ca)[T], E (&cb)[T], const E (&wa1)[T], const E (&wb1)[T])
+    {
+        if constexpr (K2 < T) {
+            ca[K2] = F::upd(F::upd(ca[K2], ca[K], row_bcast<2 * K2>(wa1[K])), cb[K], row_bcast<2 * K2>(wb1[K]));
+            cb[K2] = F::upd(F::upd(cb[K2], ca[K], row_bcast<2 * K2 + 1>(wa1[K])), cb[K],
+                            row_bcast<2 * K2 + 1>(wb1[K]));
+            multipliers2<K, K2 + 1>(ca, cb, wa1, wb1);
+        } else if constexpr (K + 2 < T) {
+            __builtin_amdgcn_sched_barrier(0);   // keep later broadcasts from being formed early (registers)
+            multipliers2<K + 1, K + 2>(ca, cb, wa1, wb1);
+        }
+    }
+
+    // M[i] -= (lane i of c) w
+    template <int I>
+    __device__ __forceinline__ void sub_rows(E (&M)[R0], E c, E w)
+    {
+        if constexpr (I < R0) {
+            row_sub_lanes4<I>(M[I], M[I + 1], M[I + 2], M[I + 3], c, w);
+            sub_rows<I + 4>(M, c, w);
         }
     }
 
@@ -162,21 +218,22 @@ struct Unit {
         }
     }
 
+    // put 1 where c holds (and v is zero)
+    static __device__ __forceinline__ void add_unit(double& v, bool c) { v += unit_if(c); }
+    static __device__ __forceinline__ void add_unit(cd& v, bool c) { v.x += unit_if(c); }
+
     template <int K>
-    __device__ __forceinline__ void top_xnor_pivots(const E* A0, int kc, bool lane_kept, E (&wa0)[T], E (&wa1)[T],
+    __device__ __forceinline__ void top_xnor_pivots(const E* A0, int kc, int lane_kept, E (&wa0)[T], E (&wa1)[T],
                                                     E (&wb0)[T], E (&wb1)[T], E& mk)
     {
         if constexpr (K < T) {
             constexpr int w = 2 * N, ra = 2 * (N - 1 - K);
-            const bool kept = (path >> (T - 1 - K)) & 1;
-            E a0 = A0[ra * w + l16], a1 = A0[ra * w + kc];
-            E b0 = A0[(ra + 1) * w + l16], b1 = A0[(ra + 1) * w + kc];
-            if (!lane_kept) a1 = b1 = F::zero();
-            if (!kept) {   // unit rows: the pivot block is the identity and changes nothing
-                a0 = a1 = b0 = b1 = F::zero();
-                if (l16 == 2 * K) a1 = F::one();
-                if (l16 == 2 * K + 1) b1 = F::one();
-            }
+            // a block left out: unit rows, so that its pivot block is the identity and changes nothing
+            const int kept = -((path >> (T - 1 - K)) & 1);
+            E a0 = keep_if(kept, A0[ra * w + l16]), a1 = keep_if(kept & lane_kept, A0[ra * w + kc]);
+            E b0 = keep_if(kept, A0[(ra + 1) * w + l16]), b1 = keep_if(kept & lane_kept, A0[(ra + 1) * w + kc]);
+            add_unit(a1, !kept && l16 == 2 * K);
+            add_unit(b1, !kept && l16 == 2 * K + 1);
             apply_xnor<0, K>(a0, a1, wa0, wa1, wb0, wb1);
             apply_xnor<0, K>(b0, b1, wa0, wa1, wb0, wb1);
             const E a00 = row_bcast<2 * K>(a1), a01 = row_bcast<2 * K + 1>(a1);
@@ -194,63 +251,107 @@ struct Unit {
     }
 
     // ---------------------------------------------------------------- row phase
-    // The child of the order-m node M that keeps row m - 2 + A (XOR) or both (XNOR, A = 1).
-    template <int m, int A>
-    __device__ __forceinline__ void child(const E (&M)[m], E (&C)[m - 2], E mk, E& mc_out)
+    // XOR: the pivots of both children of an order-m node, their reciprocals and the
+    // children's minors, in lanes m - 2 and m - 1 (one reciprocal for both).
+    template <int m>
+    __device__ __forceinline__ void pivots(const E (&M)[m], E mk, E& mkd, typename F::R& r)
     {
-        constexpr int mc = m - 2;
-        if constexpr (MODE == kXor) {
-            const E pv = row_bcast<mc + A>(M[mc + A]);
-            mc_out = F::bmul(mk, pv, 0);
-            const E w = F::rowscale(M[mc + A], F::recip(pv));
-#pragma unroll
-            for (int i = 0; i < mc; ++i) C[i] = row_upd<F, mc + A>(M[i], M[i], w);
-        } else {
-            const E a00 = row_bcast<mc>(M[mc]), a01 = row_bcast<mc + 1>(M[mc]);
-            const E a10 = row_bcast<mc>(M[mc + 1]), a11 = row_bcast<mc + 1>(M[mc + 1]);
-            const E det = F::det2(a00, a01, a10, a11);
-            mc_out = F::bmul(mk, det, 0);
-            const typename F::R r = F::recip(det);
-            const E w0 = F::rowscale(F::upd(F::bmul(M[mc], a11, 0), a01, M[mc + 1]), r);
-            const E w1 = F::rowscale(F::upd(F::bmul(M[mc + 1], a00, 0), a10, M[mc]), r);
-#pragma unroll
-            for (int i = 0; i < mc; ++i) C[i] = row_upd<F, mc + 1>(row_upd<F, mc>(M[i], M[i], w0), M[i], w1);
-        }
+        const E d = l16 == m - 1 ? M[m - 1] : M[m - 2];
+        mkd = F::bmul(mk, d, 0);
+        r = F::recip(d);
     }
 
-    // Node of order m at path p (from the root); its low bits are the place among the phase's
-    // order-8 nodes.
+    // Keep the minors of the two children (lanes m - 2 and m - 1) in this unit's slots `at`,
+    // `at` + 1; the other lanes write to a place of their own that nobody reads, which costs
+    // less than masking them.
     template <int m>
-    __device__ __forceinline__ void node(const E (&M)[m], E mk, int p, int t)
+    __device__ __forceinline__ void keep(int at, E mkd)
+    {
+        const bool own = l16 == m - 2 || l16 == m - 1;
+        (own ? &sh.mn[kSlots * (int)(threadIdx.x >> 4) + l16 - (m - 2)] : &sh.dump[threadIdx.x])[at] = mkd;
+    }
+
+    // XOR: the child that keeps row m - 2 + A from its lane's values of pivots().
+    template <int m, int A>
+    __device__ __forceinline__ void child_xor(E (&M)[m], E (&C)[m - 2], typename F::R rd)
+    {
+        constexpr int mc = m - 2;
+        const E w = F::rowscale(M[mc + A], row_bcast<mc + A>(rd));
+#pragma unroll
+        for (int i = 0; i < mc; ++i) C[i] = row_upd<F, mc + A>(M[i], M[i], w);
+    }
+
+    // The same in place (the node is not needed any more).
+    template <int m>
+    __device__ __forceinline__ void last_child_xor(E (&M)[m], typename F::R rd)
+    {
+        constexpr int mc = m - 2, P = m - 1;
+        E w = F::rowscale(M[P], row_bcast<P>(rd));
+        if (F::kComplex && l16 == P) w = F::zero();
+#pragma unroll
+        for (int i = 0; i + 4 <= mc; i += 4) row_elim4<P>(M[i], M[i + 1], M[i + 2], M[i + 3], w);
+        if constexpr (mc % 4) row_elim2<P>(M[mc - 2], M[mc - 1], w);
+    }
+
+    // XNOR: the child that keeps both rows; its minor.
+    template <int m>
+    __device__ __forceinline__ E child_xnor(const E (&M)[m], E (&C)[m - 2], E mk)
+    {
+        constexpr int mc = m - 2;
+        const E a00 = row_bcast<mc>(M[mc]), a01 = row_bcast<mc + 1>(M[mc]);
+        const E a10 = row_bcast<mc>(M[mc + 1]), a11 = row_bcast<mc + 1>(M[mc + 1]);
+        const E det = F::det2(a00, a01, a10, a11);
+        const typename F::R r = F::recip(det);
+        const E w0 = F::rowscale(F::upd(F::bmul(M[mc], a11, 0), a01, M[mc + 1]), r);
+        const E w1 = F::rowscale(F::upd(F::bmul(M[mc + 1], a00, 0), a10, M[mc]), r);
+#pragma unroll
+        for (int i = 0; i < mc; i += 2) {
+            C[i] = M[i];
+            C[i + 1] = M[i + 1];
+            row_sub2<mc>(C[i], C[i + 1], M[i], M[i + 1], w0);
+            row_sub2<mc + 1>(C[i], C[i + 1], M[i], M[i + 1], w1);
+        }
+        return F::bmul(mk, det, 0);
+    }
+
+    // The subtree of an order-m node (destroyed) down to order 8.  t: its place among the
+    // phase's nodes of its depth; LV: levels below the phase's root.
+    template <int m, int LV>
+    __device__ __forceinline__ void node(E (&M)[m], E mk, int t)
     {
         if constexpr (m == 8) {
-            const int q = (int)(threadIdx.x >> 4) * NPR + (t & (NPR - 1));
+            const int q = (int)(threadIdx.x >> 4) * NPR + t;
             if (l16 < 8) {
                 E* d = &sh.node[q * kPS + l16];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) d[i * 8] = M[i];
             }
-            if (l16 == 0) sh.mn[q] = mk;
+            if constexpr (MODE == kXnor || LV == 0) {
+                const bool own = l16 == 0;
+                (own ? &sh.mn[kSlots * (int)(threadIdx.x >> 4) + kLast] : &sh.dump[threadIdx.x])[t] = mk;
+                chk += F::fincheck(mk);
+            }
+        } else if constexpr (MODE == kXor) {
+            E mkd;
+            typename F::R rd;
+            pivots<m>(M, mk, mkd, rd);
+            keep<m>((2 << LV) - 2 + 2 * t, mkd);
+            {
+                E C[m - 2];
+                child_xor<m, 0>(M, C, rd);
+                node<m - 2, LV + 1>(C, row_bcast<m - 2>(mkd), 2 * t);
+            }
+            last_child_xor<m>(M, rd);
+            node<m - 2, LV + 1>(reinterpret_cast<E(&)[m - 2]>(M), row_bcast<m - 1>(mkd), 2 * t + 1);
         } else {
-            constexpr int d = N - m / 2 + 1;     // the children's depth
-            branch<m, 0, d>(M, mk, p, t);
-            branch<m, 1, d>(M, mk, p, t);
+            {
+                E C[m - 2];
+                const E mc = child_xnor<m>(M, C, mk);
+                node<m - 2, LV + 1>(C, mc, 2 * t + 1);
+            }
+            // the block left out: the leading part, minor unchanged
+            node<m - 2, LV + 1>(reinterpret_cast<E(&)[m - 2]>(M), mk, 2 * t);
         }
-    }
-
-    template <int m, int A, int D>
-    __device__ __forceinline__ void branch(const E (&M)[m], E mk, int p, int t)
-    {
-        E C[m - 2], mc;
-        if constexpr (MODE == kXnor && A == 0) {
-#pragma unroll
-            for (int i = 0; i < m - 2; ++i) C[i] = M[i];   // the leading part, minor unchanged
-            mc = mk;
-        } else {
-            child<m, A>(M, C, mk, mc);
-            record(D, 2 * p + A, mc);
-        }
-        node<m - 2>(C, mc, 2 * p + A, 2 * t + A);
     }
 
     // ---------------------------------------------------------------- lane phase
@@ -324,12 +425,26 @@ struct Unit {
         E lv8[8], lv4[4], lv2[2], m6;
         const bool act = lane < 4 * per;
         wave_sync();
+        if constexpr (MODE == kXor && LV8 > 0) {
+            // the minors of the row phase: slot 2^j - 2 + t is place t of level j below the
+            // phase's root, the last two slots (two phases a unit) the root's own level
+            const int j = 31 - __clz(l16 + 2), t = l16 + 2 - (1 << j);
+            const bool top2 = halves(N) == 2 && l16 >= kSlots - 2;
+            const int d = top2 ? T + 1 : T + halves(N) - 1 + j;
+            const int root = halves(N) == 2 ? 2 * path + h : path;
+            const int p = top2 ? 2 * path + l16 - (kSlots - 2) : (root << j) + t;
+            if (valid && (top2 ? h == 0 : l16 < (2 << LV8) - 2)) {
+                const E v = sh.mn[lane];
+                ob[(int64_t(1) << d) - 2 + p] = v;
+                chk += F::fincheck(v);
+            }
+        }
         if (act) {
             const E* P = &sh.node[q * kPS];
             E C[6][6];
             if constexpr (MODE == kXor) {
                 const E pv = P[(6 + a) * 8 + 6 + a];
-                m6 = F::bmul(sh.mn[q], pv, 0);
+                m6 = F::bmul(sh.mn[kSlots * (q / NPR) + kLast + q % NPR], pv, 0);
                 const typename F::R r = F::recip(pv);
                 E w[6];
 #pragma unroll
@@ -345,7 +460,7 @@ struct Unit {
                 // subtracts zero times zero
                 const E a00 = P[6 * 8 + 6], a01 = P[6 * 8 + 7], a10 = P[7 * 8 + 6], a11 = P[7 * 8 + 7];
                 const E det = F::det2(a00, a01, a10, a11);
-                m6 = a ? F::bmul(sh.mn[q], det, 0) : sh.mn[q];
+                m6 = a ? F::bmul(sh.mn[kSlots * (q / NPR) + kLast + q % NPR], det, 0) : sh.mn[kSlots * (q / NPR) + kLast + q % NPR];
                 const typename F::R r = F::recip(det);
                 E w0[6], w1[6];
 #pragma unroll
@@ -441,6 +556,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
         const E* A0 = A + b * (w * w);
         un.path = (int)(uc & ((1 << T) - 1));
         un.ob = out + b * nout;
+        un.valid = valid;
         un.wr = valid && un.l16 == 0;
         if (u0 == first || (u0 & ((1 << T) - 1)) == 0 || T < 2) {   // a matrix begins
             bool fin = true;
@@ -455,16 +571,35 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
         un.top(A0, M, mk);
         if constexpr (MODE == kXnor) un.chk += F::fincheck(mk);
         if constexpr (halves(N) == 2) {
+            E mkd = F::zero();
+            typename F::R rd{};
+            if constexpr (MODE == kXor) {
+                un.template pivots<16>(M, mk, mkd, rd);
+                un.template keep<16>(kSlots - 2, mkd);
+            }
 #pragma unroll 1
-            for (int h = 0; h < 2; ++h) {
-                if (h == 0)
-                    un.template branch<U::R0, 0, T + 1>(M, mk, un.path, 0);
-                else
-                    un.template branch<U::R0, 1, T + 1>(M, mk, un.path, 0);
+            for (int k = 0; k < 2; ++k) {
+                // XNOR: the child that keeps the block first (the other one is formed in place)
+                const int h = MODE == kXnor ? 1 - k : k;
+                if (k == 0) {
+                    E C[14];
+                    if constexpr (MODE == kXor) {
+                        un.template child_xor<16, 0>(M, C, rd);
+                        un.template node<14, 0>(C, row_bcast<14>(mkd), 0);
+                    } else {
+                        const E mc = un.template child_xnor<16>(M, C, mk);
+                        un.template node<14, 0>(C, mc, 0);
+                    }
+                } else if constexpr (MODE == kXor) {
+                    un.template last_child_xor<16>(M, rd);
+                    un.template node<14, 0>(reinterpret_cast<E(&)[14]>(M), row_bcast<15>(mkd), 0);
+                } else {
+                    un.template node<14, 0>(reinterpret_cast<E(&)[14]>(M), mk, 0);
+                }
                 un.lanes(out, u0, units, h);
             }
         } else {
-            un.template node<U::R0>(M, mk, un.path, 0);
+            un.template node<U::R0, 0>(M, mk, 0);
             un.lanes(out, u0, units, 0);
         }
         // the last units of a matrix here: its info
