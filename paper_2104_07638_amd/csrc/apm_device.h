@@ -142,6 +142,16 @@ __device__ __forceinline__ cd operator*(cd a, cd b) { return {fma(a.x, b.x, -a.y
 __device__ __forceinline__ cd operator-(cd a, cd b) { return {a.x - b.x, a.y - b.y}; }
 __device__ __forceinline__ cd operator*(double s, cd a) { return {s * a.x, s * a.y}; }
 
+// A value held in registers from here on: a plain copy of a structure is a memory copy to the
+// compiler, which a scheduling barrier behind it sends through scratch memory.
+__device__ __forceinline__ double load_reg(const double* p) { return *p; }
+__device__ __forceinline__ cd load_reg(const cd* p)
+{
+    typedef double v2d __attribute__((ext_vector_type(2)));
+    const v2d v = *reinterpret_cast<const v2d*>(p);
+    return {v.x, v.y};
+}
+
 template <int P>
 __device__ __forceinline__ cd row_bcast(cd v)
 {

@@ -49,13 +49,6 @@ struct Lds {
     typename F::E dump[64 + kSlots];
 };
 
-// a - c w with c = lane P's value of src
-template <class F, int P>
-__device__ __forceinline__ typename F::E row_upd(typename F::E a, typename F::E src, typename F::E w)
-{
-    return F::upd(a, row_bcast<P>(src), w);
-}
-
 // v where m is all ones, zero where m is zero (no branch around the load of v)
 __device__ __forceinline__ double keep_if(int m, double v)
 {
@@ -63,6 +56,15 @@ __device__ __forceinline__ double keep_if(int m, double v)
 }
 __device__ __forceinline__ cd keep_if(int m, cd v) { return {keep_if(m, v.x), keep_if(m, v.y)}; }
 __device__ __forceinline__ double unit_if(bool c) { return __hiloint2double(c ? 0x3FF00000 : 0, 0); }
+
+// The lane number, new to the compiler at every call: addresses made from it are formed where
+// they are used instead of being kept in registers across the whole loop over the units.
+__device__ __forceinline__ int lane_here()
+{
+    int l = (int)threadIdx.x;
+    asm volatile("" : "+v"(l));
+    return l;
+}
 
 template <class F, int N, int MODE>
 struct Unit {
@@ -96,15 +98,23 @@ struct Unit {
             // lane t's kept column: the chosen one of block N - 1 - t
             const int t = l16 < T ? l16 : T - 1;
             const int kc = 2 * (N - 1 - t) + ((path >> (T - 1 - t)) & 1);
-            E w0[T], w1[T];
-            top_xor_pivots<0>(A0, kc, w0, w1, mk);
-            // the undecided rows' multipliers with a row per lane: the kept columns eliminated
-            // for all 16 rows at once
-            E c[T];
+            // every load first (one memory round trip; left alone, the compiler saves
+            // registers by loading a row or two at a time): the kept rows, the kept columns
+            // with a row per lane, the undecided rows
+            E w0[T], w1[T], c[T];
 #pragma unroll
-            for (int k = 0; k < T; ++k) c[k] = A0[l16 * w + 2 * (N - 1 - k) + ((path >> (T - 1 - k)) & 1)];
+            for (int k = 0; k < T; ++k) {
+                const int row = 2 * (N - 1 - k) + ((path >> (T - 1 - k)) & 1);
+                w0[k] = load_reg(&A0[row * w + l16]);
+                w1[k] = load_reg(&A0[row * w + kc]);
+            }
 #pragma unroll
-            for (int i = 0; i < R0; ++i) M[i] = A0[i * w + l16];
+            for (int k = 0; k < T; ++k) c[k] = load_reg(&A0[l16 * w + 2 * (N - 1 - k) + ((path >> (T - 1 - k)) & 1)]);
+#pragma unroll
+            for (int i = 0; i < R0; ++i) M[i] = load_reg(&A0[i * w + l16]);
+            __builtin_amdgcn_sched_barrier(0);
+            top_xor_pivots<0>(w0, w1, mk);
+            // the undecided rows' multipliers: the kept columns eliminated for all 16 rows at once
             multipliers<0, 1>(c, w1);
 #pragma unroll
             for (int k = 0; k < T; ++k) sub_rows<0>(M, c[k], w0[k]);
@@ -112,22 +122,37 @@ struct Unit {
             // lane 2 t + r's kept column: column r of block N - 1 - t (zero if left out)
             const int t = l16 < 2 * T ? l16 >> 1 : T - 1;
             const int kc = 2 * (N - 1 - t) + (l16 & 1);
-            const int kept = -((path >> (T - 1 - t)) & 1);   // as a bit mask
-            E wa0[T], wa1[T], wb0[T], wb1[T];
-            top_xnor_pivots<0>(A0, kc, kept, wa0, wa1, wb0, wb1, mk);
-            __builtin_amdgcn_sched_barrier(0);   // the rows are loaded once the pivots' registers are free
-            E ca[T], cb[T];
+            const int lane_kept = -((path >> (T - 1 - t)) & 1);   // as a bit mask
+            // the loads in two groups: the pivot blocks' rows and columns, then (their registers
+            // free again) the undecided rows
+            E wa0[T], wa1[T], wb0[T], wb1[T], ca[T], cb[T];
+#pragma unroll
+            for (int k = 0; k < T; ++k) {
+                const E* p = A0 + 2 * (N - 1 - k) * w;
+                wa0[k] = load_reg(&p[l16]);
+                wa1[k] = load_reg(&p[kc]);
+                wb0[k] = load_reg(&p[w + l16]);
+                wb1[k] = load_reg(&p[w + kc]);
+            }
 #pragma unroll
             for (int k = 0; k < T; ++k) {
                 const E* p = A0 + l16 * w + 2 * (N - 1 - k);
-                const int in = -((path >> (T - 1 - k)) & 1);
-                ca[k] = keep_if(in, p[0]);
-                cb[k] = keep_if(in, p[1]);
+                ca[k] = load_reg(&p[0]);
+                cb[k] = load_reg(&p[1]);
             }
-            multipliers2<0, 1>(ca, cb, wa1, wb1);
+            __builtin_amdgcn_sched_barrier(0);
+            top_xnor_pivots<0>(lane_kept, wa0, wa1, wb0, wb1, mk);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 0; i < R0; ++i) M[i] = A0[i * w + l16];
+            for (int i = 0; i < R0; ++i) M[i] = load_reg(&A0[i * w + l16]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < T; ++k) {
+                const int in = -((path >> (T - 1 - k)) & 1);
+                ca[k] = keep_if(in, ca[k]);
+                cb[k] = keep_if(in, cb[k]);
+            }
+            multipliers2<0, 1>(ca, cb, wa1, wb1);
 #pragma unroll
             for (int k = 0; k < T; ++k) {
                 sub_rows<0>(M, ca[k], wa0[k]);
@@ -168,8 +193,13 @@ struct Unit {
     __device__ __forceinline__ void sub_rows(E (&M)[R0], E c, E w)
     {
         if constexpr (I < R0) {
-            row_sub_lanes4<I>(M[I], M[I + 1], M[I + 2], M[I + 3], c, w);
-            sub_rows<I + 4>(M, c, w);
+            if constexpr (F::kComplex) {
+                row_sub_lanes<I>(M[I], M[I + 1], M[I + 2], M[I + 3], c, w);
+                sub_rows<I + 4>(M, c, w);
+            } else {
+                row_sub_lanes<I>(M[I], M[I + 1], M[I + 2], M[I + 3], M[I + 4], M[I + 5], M[I + 6], M[I + 7], c, w);
+                sub_rows<I + 8>(M, c, w);
+            }
         }
     }
 
@@ -185,13 +215,13 @@ struct Unit {
         }
     }
 
+    // kept row K (from the input) to its scaled pivot row, K upwards
     template <int K>
-    __device__ __forceinline__ void top_xor_pivots(const E* A0, int kc, E (&w0)[T], E (&w1)[T], E& mk)
+    __device__ __forceinline__ void top_xor_pivots(E (&w0)[T], E (&w1)[T], E& mk)
     {
         if constexpr (K < T) {
             constexpr int low = T - 1 - K;
-            const int row = 2 * (N - 1 - K) + ((path >> low) & 1);
-            E a0 = A0[row * (2 * N) + l16], a1 = A0[row * (2 * N) + kc];
+            E a0 = w0[K], a1 = w1[K];
             apply_xor<0, K>(a0, a1, w0, w1);
             const E pv = row_bcast<K>(a1);
             mk = F::bmul(mk, pv, 0);
@@ -201,7 +231,7 @@ struct Unit {
             const typename F::R r = F::recip(pv);
             w0[K] = F::rowscale(a0, r);
             w1[K] = F::rowscale(a1, r);
-            top_xor_pivots<K + 1>(A0, kc, w0, w1, mk);
+            top_xor_pivots<K + 1>(w0, w1, mk);
         }
     }
 
@@ -223,15 +253,14 @@ struct Unit {
     static __device__ __forceinline__ void add_unit(cd& v, bool c) { v.x += unit_if(c); }
 
     template <int K>
-    __device__ __forceinline__ void top_xnor_pivots(const E* A0, int kc, int lane_kept, E (&wa0)[T], E (&wa1)[T],
+    __device__ __forceinline__ void top_xnor_pivots(int lane_kept, E (&wa0)[T], E (&wa1)[T],
                                                     E (&wb0)[T], E (&wb1)[T], E& mk)
     {
         if constexpr (K < T) {
-            constexpr int w = 2 * N, ra = 2 * (N - 1 - K);
             // a block left out: unit rows, so that its pivot block is the identity and changes nothing
             const int kept = -((path >> (T - 1 - K)) & 1);
-            E a0 = keep_if(kept, A0[ra * w + l16]), a1 = keep_if(kept & lane_kept, A0[ra * w + kc]);
-            E b0 = keep_if(kept, A0[(ra + 1) * w + l16]), b1 = keep_if(kept & lane_kept, A0[(ra + 1) * w + kc]);
+            E a0 = keep_if(kept, wa0[K]), a1 = keep_if(kept & lane_kept, wa1[K]);
+            E b0 = keep_if(kept, wb0[K]), b1 = keep_if(kept & lane_kept, wb1[K]);
             add_unit(a1, !kept && l16 == 2 * K);
             add_unit(b1, !kept && l16 == 2 * K + 1);
             apply_xnor<0, K>(a0, a1, wa0, wa1, wb0, wb1);
@@ -246,7 +275,7 @@ struct Unit {
             wb1[K] = F::rowscale(F::upd(F::bmul(b1, a00, 0), a10, a1), r);
             if (kept) mk = F::bmul(mk, det, 0);
             chk += F::fincheck(mk);
-            top_xnor_pivots<K + 1>(A0, kc, lane_kept, wa0, wa1, wb0, wb1, mk);
+            top_xnor_pivots<K + 1>(lane_kept, wa0, wa1, wb0, wb1, mk);
         }
     }
 
@@ -271,26 +300,77 @@ struct Unit {
         (own ? &sh.mn[kSlots * (int)(threadIdx.x >> 4) + l16 - (m - 2)] : &sh.dump[threadIdx.x])[at] = mkd;
     }
 
-    // XOR: the child that keeps row m - 2 + A from its lane's values of pivots().
-    template <int m, int A>
-    __device__ __forceinline__ void child_xor(E (&M)[m], E (&C)[m - 2], typename F::R rd)
+    // rows 0 .. n-1 of the child that keeps row P, in blocks of rows
+    template <int P, int n, int m>
+    __device__ __forceinline__ void child_rows(E (&M)[m], E (&C)[m - 2], E w)
     {
-        constexpr int mc = m - 2;
-        const E w = F::rowscale(M[mc + A], row_bcast<mc + A>(rd));
-#pragma unroll
-        for (int i = 0; i < mc; ++i) C[i] = row_upd<F, mc + A>(M[i], M[i], w);
+        if constexpr (n == 6 && !F::kComplex) {
+            row_child<P>(C[0], C[1], C[2], C[3], C[4], C[5], M[0], M[1], M[2], M[3], M[4], M[5], w);
+        } else if constexpr (n >= 4) {
+            row_child<P>(C[n - 4], C[n - 3], C[n - 2], C[n - 1], M[n - 4], M[n - 3], M[n - 2], M[n - 1], w);
+            child_rows<P, n - 4>(M, C, w);
+        } else if constexpr (n > 0) {
+            row_child<P>(C[n - 2], C[n - 1], M[n - 2], M[n - 1], w);
+            child_rows<P, n - 2>(M, C, w);
+        }
     }
 
-    // The same in place (the node is not needed any more).
+    // the same in place
+    template <int P, int n, int m>
+    __device__ __forceinline__ void elim_rows(E (&M)[m], E w)
+    {
+        if constexpr (n == 8 && !F::kComplex) {
+            row_elim<P>(M[0], M[1], M[2], M[3], M[4], M[5], M[6], M[7], w);
+        } else if constexpr (n >= 6 && n != 8) {
+            row_elim<P>(M[n - 6], M[n - 5], M[n - 4], M[n - 3], M[n - 2], M[n - 1], w);
+            elim_rows<P, n - 6>(M, w);
+        } else if constexpr (n >= 4) {
+            row_elim<P>(M[n - 4], M[n - 3], M[n - 2], M[n - 1], w);
+            elim_rows<P, n - 4>(M, w);
+        } else if constexpr (n > 0) {
+            row_elim<P>(M[n - 2], M[n - 1], w);
+        }
+    }
+
+    // XOR: the child that keeps row m - 2 (rd: the reciprocals of pivots()).  Its last rows
+    // come first and its own pivots right after them, so that their chain of dependent
+    // operations runs beside the other rows' updates.
     template <int m>
-    __device__ __forceinline__ void last_child_xor(E (&M)[m], typename F::R rd)
+    __device__ __forceinline__ void child_xor(E (&M)[m], E (&C)[m - 2], typename F::R rd, E mk, E& cmkd,
+                                              typename F::R& crd)
+    {
+        constexpr int mc = m - 2, P = mc;
+        const E w = F::rowscale(M[P], row_bcast<P>(rd));
+        row_child<P>(C[mc - 2], C[mc - 1], M[mc - 2], M[mc - 1], w);
+        if constexpr (mc > 8) pivots<mc>(C, mk, cmkd, crd);
+        child_rows<P, mc - 2>(M, C, w);
+    }
+
+    // The child that keeps row m - 1, in place (the node is not needed any more).
+    template <int m>
+    __device__ __forceinline__ void last_child_xor(E (&M)[m], typename F::R rd, E mk, E& cmkd, typename F::R& crd)
     {
         constexpr int mc = m - 2, P = m - 1;
         E w = F::rowscale(M[P], row_bcast<P>(rd));
-        if (F::kComplex && l16 == P) w = F::zero();
-#pragma unroll
-        for (int i = 0; i + 4 <= mc; i += 4) row_elim4<P>(M[i], M[i + 1], M[i + 2], M[i + 3], w);
-        if constexpr (mc % 4) row_elim2<P>(M[mc - 2], M[mc - 1], w);
+        if constexpr (F::kComplex)
+            row_elim_first<P>(M[mc - 2], M[mc - 1], w, unit_if(l16 != P));
+        else
+            row_elim<P>(M[mc - 2], M[mc - 1], w);
+        if constexpr (mc > 8) pivots<mc>(reinterpret_cast<E(&)[mc]>(M), mk, cmkd, crd);
+        elim_rows<P, mc - 2>(M, w);
+    }
+
+    // XNOR: rows 0 .. n-1 of the child that keeps both rows
+    template <int n, int m>
+    __device__ __forceinline__ void child2_rows(const E (&M)[m], E (&C)[m - 2], E w0, E w1)
+    {
+        constexpr int P = m - 2;
+        if constexpr (n >= 4) {
+            row_child2<P>(C[n - 4], C[n - 3], C[n - 2], C[n - 1], M[n - 4], M[n - 3], M[n - 2], M[n - 1], w0, w1);
+            child2_rows<n - 4>(M, C, w0, w1);
+        } else if constexpr (n > 0) {
+            row_child2<P>(C[n - 2], C[n - 1], M[n - 2], M[n - 1], w0, w1);
+        }
     }
 
     // XNOR: the child that keeps both rows; its minor.
@@ -298,26 +378,21 @@ struct Unit {
     __device__ __forceinline__ E child_xnor(const E (&M)[m], E (&C)[m - 2], E mk)
     {
         constexpr int mc = m - 2;
-        const E a00 = row_bcast<mc>(M[mc]), a01 = row_bcast<mc + 1>(M[mc]);
-        const E a10 = row_bcast<mc>(M[mc + 1]), a11 = row_bcast<mc + 1>(M[mc + 1]);
+        E a00, a01, a10, a11;
+        row_block_after<mc>(M[mc], M[mc + 1], a00, a01, a10, a11);
         const E det = F::det2(a00, a01, a10, a11);
         const typename F::R r = F::recip(det);
         const E w0 = F::rowscale(F::upd(F::bmul(M[mc], a11, 0), a01, M[mc + 1]), r);
         const E w1 = F::rowscale(F::upd(F::bmul(M[mc + 1], a00, 0), a10, M[mc]), r);
-#pragma unroll
-        for (int i = 0; i < mc; i += 2) {
-            C[i] = M[i];
-            C[i + 1] = M[i + 1];
-            row_sub2<mc>(C[i], C[i + 1], M[i], M[i + 1], w0);
-            row_sub2<mc + 1>(C[i], C[i + 1], M[i], M[i + 1], w1);
-        }
+        child2_rows<mc>(M, C, w0, w1);
         return F::bmul(mk, det, 0);
     }
 
     // The subtree of an order-m node (destroyed) down to order 8.  t: its place among the
-    // phase's nodes of its depth; LV: levels below the phase's root.
+    // phase's nodes of its depth; LV: levels below the phase's root; mkd, rd: its pivots()
+    // (XOR above order 8).
     template <int m, int LV>
-    __device__ __forceinline__ void node(E (&M)[m], E mk, int t)
+    __device__ __forceinline__ void node(E (&M)[m], E mk, E mkd, typename F::R rd, int t)
     {
         if constexpr (m == 8) {
             const int q = (int)(threadIdx.x >> 4) * NPR + t;
@@ -332,29 +407,52 @@ struct Unit {
                 chk += F::fincheck(mk);
             }
         } else if constexpr (MODE == kXor) {
-            E mkd;
-            typename F::R rd;
-            pivots<m>(M, mk, mkd, rd);
             keep<m>((2 << LV) - 2 + 2 * t, mkd);
+            E cmkd = F::zero();
+            typename F::R crd{};
             {
                 E C[m - 2];
-                child_xor<m, 0>(M, C, rd);
-                node<m - 2, LV + 1>(C, row_bcast<m - 2>(mkd), 2 * t);
+                const E mk0 = row_bcast<m - 2>(mkd);
+                child_xor(M, C, rd, mk0, cmkd, crd);
+                node<m - 2, LV + 1>(C, mk0, cmkd, crd, 2 * t);
             }
-            last_child_xor<m>(M, rd);
-            node<m - 2, LV + 1>(reinterpret_cast<E(&)[m - 2]>(M), row_bcast<m - 1>(mkd), 2 * t + 1);
+            const E mk1 = row_bcast<m - 1>(mkd);
+            last_child_xor(M, rd, mk1, cmkd, crd);
+            node<m - 2, LV + 1>(reinterpret_cast<E(&)[m - 2]>(M), mk1, cmkd, crd, 2 * t + 1);
         } else {
             {
                 E C[m - 2];
-                const E mc = child_xnor<m>(M, C, mk);
-                node<m - 2, LV + 1>(C, mc, 2 * t + 1);
+                const E mc = child_xnor(M, C, mk);
+                node<m - 2, LV + 1>(C, mc, mkd, rd, 2 * t + 1);
             }
             // the block left out: the leading part, minor unchanged
-            node<m - 2, LV + 1>(reinterpret_cast<E(&)[m - 2]>(M), mk, 2 * t);
+            node<m - 2, LV + 1>(reinterpret_cast<E(&)[m - 2]>(M), mk, mkd, rd, 2 * t);
         }
     }
 
     // ---------------------------------------------------------------- lane phase
+    // k[j] = a[j] - c w[j] (F::upd), the dependent halves of the complex updates apart
+    template <int n>
+    static __device__ __forceinline__ void lane_row(double* k, const double* a, double c, const double* w)
+    {
+#pragma unroll
+        for (int j = 0; j < n; ++j) k[j] = fma(-c, w[j], a[j]);
+    }
+    template <int n>
+    static __device__ __forceinline__ void lane_row(cd* k, const cd* a, cd c, const cd* w)
+    {
+#pragma unroll
+        for (int j = 0; j < n; ++j) {
+            k[j].x = fma(c.y, w[j].y, a[j].x);
+            k[j].y = fma(-c.y, w[j].x, a[j].y);
+        }
+#pragma unroll
+        for (int j = 0; j < n; ++j) {
+            k[j].x = fma(-c.x, w[j].x, k[j].x);
+            k[j].y = fma(-c.x, w[j].y, k[j].y);
+        }
+    }
+
     // A lane's order-m node: its minors below, leaves (and, XOR, the depths above) in order.
     template <int m>
     __device__ __forceinline__ void leaf_levels(const E (&C)[m][m], E mk, E* lv8, E* lv4, E* lv2, int t)
@@ -368,12 +466,11 @@ struct Unit {
                 mk2 = F::bmul(mk, pv, 0);
                 if constexpr (mc > 0) {
                     const typename F::R r = F::recip(pv);
+                    E w[mc];
 #pragma unroll
-                    for (int j = 0; j < mc; ++j) {
-                        const E wj = F::rowscale(C[mc + a][j], r);
+                    for (int j = 0; j < mc; ++j) w[j] = F::rowscale(C[mc + a][j], r);
 #pragma unroll
-                        for (int i = 0; i < mc; ++i) K[i][j] = F::upd(C[i][j], C[i][mc + a], wj);
-                    }
+                    for (int i = 0; i < mc; ++i) lane_row<mc>(K[i], C[i], C[i][mc + a], w);
                 }
             } else if (a == 0) {
                 mk2 = mk;
@@ -389,12 +486,16 @@ struct Unit {
                 mk2 = F::bmul(mk, det, 0);
                 if constexpr (mc > 0) {
                     const typename F::R r = F::recip(det);
+                    E w0[mc], w1[mc];
 #pragma unroll
                     for (int j = 0; j < mc; ++j) {
-                        const E w0 = F::rowscale(F::upd(F::bmul(C[mc][j], a11, 0), a01, C[mc + 1][j]), r);
-                        const E w1 = F::rowscale(F::upd(F::bmul(C[mc + 1][j], a00, 0), a10, C[mc][j]), r);
+                        w0[j] = F::rowscale(F::upd(F::bmul(C[mc][j], a11, 0), a01, C[mc + 1][j]), r);
+                        w1[j] = F::rowscale(F::upd(F::bmul(C[mc + 1][j], a00, 0), a10, C[mc][j]), r);
+                    }
 #pragma unroll
-                        for (int i = 0; i < mc; ++i) K[i][j] = F::upd(F::upd(C[i][j], C[i][mc], w0), C[i][mc + 1], w1);
+                    for (int i = 0; i < mc; ++i) {
+                        lane_row<mc>(K[i], C[i], C[i][mc], w0);
+                        lane_row<mc>(K[i], K[i], C[i][mc + 1], w1);
                     }
                 }
             }
@@ -412,7 +513,40 @@ struct Unit {
         }
     }
 
+    // the leading 6 x 6 part of an order-8 node
+    static __device__ __forceinline__ void load_leading(const E* P, E (&C)[6][6])
+    {
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+#pragma unroll
+            for (int j = 0; j < 6; ++j) C[i][j] = load_reg(&P[i * 8 + j]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
     double chk_lane = 0.0;   // of the minors formed in the lane phase (lanes grouped by parent)
+
+    // The staged minors (W a lane, W + 1 apart) to a depth's place in the output, 64 at a time:
+    // all reads, then all stores.
+    template <int W, int IT = 0>
+    __device__ __forceinline__ void flush(const E* st, E* out, int64_t u0, int64_t units, int h, int lane)
+    {
+        constexpr int seg = 2 * NPR * W;              // contiguous minors of a unit
+        constexpr int64_t nout = MODE == kXor ? (int64_t(2) << N) - 2 : int64_t(1) << N;
+        if constexpr (IT * 64 < 4 * seg) {
+            const int e = IT * 64 + lane;
+            const E v = load_reg(&st[IT * (64 / W) * (W + 1) + (lane / W) * (W + 1) + lane % W]);
+            flush<W, IT + 1>(st, out, u0, units, h, lane);
+            // with whole wavefronts in a unit the unit is known at compile time
+            const int r = seg >= 64 ? IT * 64 / seg : e / seg;
+            const int64_t u = u0 + r;
+            if ((4 * seg >= 64 || e < 4 * seg) && (T >= 2 || u < units)) {
+                E* o = out + ((u >> T) * nout + ((u & ((1 << T) - 1)) * halves(N) + h) * seg);
+                o[e - r * seg] = v;
+            }
+        } else {
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
 
     // The order-8 nodes in LDS to their minors: lane 2 q + a takes child a of node q.  `u0`:
     // the unit of row 0, `units`: their number, `h`: which half of the units' nodes.
@@ -420,10 +554,11 @@ struct Unit {
     {
         constexpr int per = 2 * NPR;               // lanes of a unit
         constexpr int64_t nout = MODE == kXor ? (int64_t(2) << N) - 2 : int64_t(1) << N;
-        const int lane = threadIdx.x;
+        // (the addresses formed anew cost the real kernels, which have registers to spare, 6%)
+        const int lane = F::kComplex ? lane_here() : (int)threadIdx.x, l16 = lane & 15;
         const int q = lane >> 1, a = lane & 1;
         E lv8[8], lv4[4], lv2[2], m6;
-        const bool act = lane < 4 * per;
+        const bool act = 4 * per == 64 || lane < 4 * per;
         wave_sync();
         if constexpr (MODE == kXor && LV8 > 0) {
             // the minors of the row phase: slot 2^j - 2 + t is place t of level j below the
@@ -442,38 +577,52 @@ struct Unit {
         if (act) {
             const E* P = &sh.node[q * kPS];
             E C[6][6];
+            // every read first: 49 to 63 in flight, one LDS round trip
+            const E mq = load_reg(&sh.mn[kSlots * (q / NPR) + kLast + q % NPR]);
             if constexpr (MODE == kXor) {
-                const E pv = P[(6 + a) * 8 + 6 + a];
-                m6 = F::bmul(sh.mn[kSlots * (q / NPR) + kLast + q % NPR], pv, 0);
+                const E pv = load_reg(&P[(6 + a) * 8 + 6 + a]);
+                E w[6], c[6];
+#pragma unroll
+                for (int j = 0; j < 6; ++j) w[j] = load_reg(&P[(6 + a) * 8 + j]);
+#pragma unroll
+                for (int i = 0; i < 6; ++i) c[i] = load_reg(&P[i * 8 + 6 + a]);
+                load_leading(P, C);
+                m6 = F::bmul(mq, pv, 0);
                 const typename F::R r = F::recip(pv);
-                E w[6];
 #pragma unroll
-                for (int j = 0; j < 6; ++j) w[j] = F::rowscale(P[(6 + a) * 8 + j], r);
+                for (int j = 0; j < 6; ++j) w[j] = F::rowscale(w[j], r);
 #pragma unroll
-                for (int i = 0; i < 6; ++i) {
-                    const E c = P[i * 8 + 6 + a];
-#pragma unroll
-                    for (int j = 0; j < 6; ++j) C[i][j] = F::upd(P[i * 8 + j], c, w[j]);
-                }
+                for (int i = 0; i < 6; ++i) lane_row<6>(C[i], C[i], c[i], w);
             } else {
                 // both children in one instruction stream: the one that leaves the block out
                 // subtracts zero times zero
-                const E a00 = P[6 * 8 + 6], a01 = P[6 * 8 + 7], a10 = P[7 * 8 + 6], a11 = P[7 * 8 + 7];
-                const E det = F::det2(a00, a01, a10, a11);
-                m6 = a ? F::bmul(sh.mn[kSlots * (q / NPR) + kLast + q % NPR], det, 0) : sh.mn[kSlots * (q / NPR) + kLast + q % NPR];
-                const typename F::R r = F::recip(det);
-                E w0[6], w1[6];
+                const E a00 = load_reg(&P[6 * 8 + 6]), a01 = load_reg(&P[6 * 8 + 7]), a10 = load_reg(&P[7 * 8 + 6]), a11 = load_reg(&P[7 * 8 + 7]);
+                E p0[6], p1[6], c0[6], c1[6];
 #pragma unroll
                 for (int j = 0; j < 6; ++j) {
-                    const E p0 = P[6 * 8 + j], p1 = P[7 * 8 + j];
-                    w0[j] = a ? F::rowscale(F::upd(F::bmul(p0, a11, 0), a01, p1), r) : F::zero();
-                    w1[j] = a ? F::rowscale(F::upd(F::bmul(p1, a00, 0), a10, p0), r) : F::zero();
+                    p0[j] = load_reg(&P[6 * 8 + j]);
+                    p1[j] = load_reg(&P[7 * 8 + j]);
+                }
+                const E det = F::det2(a00, a01, a10, a11);
+                m6 = a ? F::bmul(mq, det, 0) : mq;
+                const typename F::R r = F::recip(det);
+                load_leading(P, C);
+#pragma unroll
+                for (int i = 0; i < 6; ++i) {
+                    c0[i] = load_reg(&P[i * 8 + 6]);
+                    c1[i] = load_reg(&P[i * 8 + 7]);
+                }
+                const int in = -a;
+#pragma unroll
+                for (int j = 0; j < 6; ++j) {
+                    const E t = p0[j];
+                    p0[j] = keep_if(in, F::rowscale(F::upd(F::bmul(t, a11, 0), a01, p1[j]), r));
+                    p1[j] = keep_if(in, F::rowscale(F::upd(F::bmul(p1[j], a00, 0), a10, t), r));
                 }
 #pragma unroll
                 for (int i = 0; i < 6; ++i) {
-                    const E c0 = a ? P[i * 8 + 6] : F::zero(), c1 = a ? P[i * 8 + 7] : F::zero();
-#pragma unroll
-                    for (int j = 0; j < 6; ++j) C[i][j] = F::upd(F::upd(P[i * 8 + j], c0, w0[j]), c1, w1[j]);
+                    lane_row<6>(C[i], C[i], keep_if(in, c0[i]), p0);
+                    lane_row<6>(C[i], C[i], keep_if(in, c1[i]), p1);
                 }
             }
             chk_lane += F::fincheck(m6);
@@ -489,7 +638,7 @@ struct Unit {
 #pragma unroll
                 for (int c = 0; c < 4; ++c) st4[lane * 5 + c] = lv4[c];
                 const int64_t u = u0 + lane / per;
-                if (u < units) {
+                if (T >= 2 || u < units) {
                     const int64_t b = u >> T;
                     // this lane's node's path: the unit's, the half, its place
                     const int s = (((int)(u & ((1 << T) - 1)) * halves(N) + h) * per) + lane % per;
@@ -503,27 +652,11 @@ struct Unit {
         }
         wave_sync();
         static_assert(64 * 14 <= kParents * kPS, "the staged minors fit the nodes' place");
-        auto flush = [&](const E* st, int64_t base, auto width) {
-            constexpr int W = decltype(width)::value;     // minors a lane
-            constexpr int seg = per * W;                  // contiguous minors of a unit
-#pragma unroll
-            for (int it = 0; it < (4 * seg + 63) / 64; ++it) {
-                const int e = it * 64 + lane;
-                // with whole wavefronts in a unit the unit is known at compile time
-                const int r = seg >= 64 ? it * 64 / seg : e / seg;
-                const int64_t u = u0 + r;
-                if (e < 4 * seg && u < units) {
-                    const int64_t b = u >> T;
-                    E* o = out + (b * nout + base + ((u & ((1 << T) - 1)) * halves(N) + h) * seg);
-                    o[e - r * seg] = st[(e / W) * (W + 1) + e % W];
-                }
-            }
-        };
         if constexpr (MODE == kXor) {
-            flush(st8, (int64_t(1) << N) - 2, std::integral_constant<int, 8>{});
-            flush(st4, (int64_t(1) << (N - 1)) - 2, std::integral_constant<int, 4>{});
+            flush<8>(st8, out + ((int64_t(1) << N) - 2), u0, units, h, lane);
+            flush<4>(st4, out + ((int64_t(1) << (N - 1)) - 2), u0, units, h, lane);
         } else {
-            flush(st8, 0, std::integral_constant<int, 8>{});
+            flush<8>(st8, out, u0, units, h, lane);
         }
         wave_sync();                               // before the next nodes overwrite the stage
     }
@@ -550,7 +683,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
     bool finite = true;
     for (int64_t u0 = first; u0 < first + per_wave && u0 < units; u0 += 4) {
         const int64_t u = u0 + (lane >> 4);
-        const bool valid = u < units;
+        const bool valid = T >= 2 || u < units;   // T >= 2: whole groups of four
         const int64_t uc = valid ? u : units - 1;
         const int64_t b = uc >> T;
         const E* A0 = A + b * (w * w);
@@ -581,25 +714,32 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
             for (int k = 0; k < 2; ++k) {
                 // XNOR: the child that keeps the block first (the other one is formed in place)
                 const int h = MODE == kXnor ? 1 - k : k;
+                E cmkd = F::zero();
+                typename F::R crd{};
                 if (k == 0) {
                     E C[14];
                     if constexpr (MODE == kXor) {
-                        un.template child_xor<16, 0>(M, C, rd);
-                        un.template node<14, 0>(C, row_bcast<14>(mkd), 0);
+                        const E mk0 = row_bcast<14>(mkd);
+                        un.child_xor(M, C, rd, mk0, cmkd, crd);
+                        un.template node<14, 0>(C, mk0, cmkd, crd, 0);
                     } else {
-                        const E mc = un.template child_xnor<16>(M, C, mk);
-                        un.template node<14, 0>(C, mc, 0);
+                        const E mc = un.child_xnor(M, C, mk);
+                        un.template node<14, 0>(C, mc, cmkd, crd, 0);
                     }
                 } else if constexpr (MODE == kXor) {
-                    un.template last_child_xor<16>(M, rd);
-                    un.template node<14, 0>(reinterpret_cast<E(&)[14]>(M), row_bcast<15>(mkd), 0);
+                    const E mk1 = row_bcast<15>(mkd);
+                    un.last_child_xor(M, rd, mk1, cmkd, crd);
+                    un.template node<14, 0>(reinterpret_cast<E(&)[14]>(M), mk1, cmkd, crd, 0);
                 } else {
-                    un.template node<14, 0>(reinterpret_cast<E(&)[14]>(M), mk, 0);
+                    un.template node<14, 0>(reinterpret_cast<E(&)[14]>(M), mk, cmkd, crd, 0);
                 }
                 un.lanes(out, u0, units, h);
             }
         } else {
-            un.template node<U::R0, 0>(M, mk, 0);
+            E mkd = F::zero();
+            typename F::R rd{};
+            if constexpr (MODE == kXor && U::R0 > 8) un.template pivots<U::R0>(M, mk, mkd, rd);
+            un.template node<U::R0, 0>(M, mk, mkd, rd, 0);
             un.lanes(out, u0, units, 0);
         }
         // the last units of a matrix here: its info
