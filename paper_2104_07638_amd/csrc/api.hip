@@ -125,7 +125,7 @@ int32_t* get_topq(hipStream_t st, int64_t batch, int32_t* cap_out, TopQueue** q_
     return static_cast<int32_t*>(q.buf);
 }
 
-// Per-(device, stream) workspace of the XOR minors' top levels (node matrices), grown on
+// Per-(device, stream) workspace of the NAND minors (top-level node matrices, flags), grown on
 // demand outside stream capture; calls on one stream are ordered by the stream.
 struct XorWs {
     void* buf = nullptr;
@@ -980,9 +980,11 @@ apm_status block_minors(int mode, apm_dtype dt, const void* A, const apm_batch* 
     L.mode = mode;
     L.ws_stride = apm::xor_ws_elems(L.n, mode);
     if (L.ws_stride > 0) {
-        const size_t bytes = (size_t)L.ws_stride * (size_t)bd->batch * (dt == APM_C128 ? 16 : 8);
-        apm_status s = get_xor_ws((hipStream_t)stream, bytes, &L.ws);
+        const size_t nodes = (size_t)L.ws_stride * (size_t)bd->batch * (dt == APM_C128 ? 16 : 8);
+        const size_t flags = apm::nand_flags(L.n, mode) ? (size_t)bd->batch * 4 : 0;
+        apm_status s = get_xor_ws((hipStream_t)stream, nodes + flags, &L.ws);
         if (s != APM_OK) return s;
+        if (flags) L.flag = reinterpret_cast<int32_t*>(static_cast<char*>(L.ws) + nodes);
     }
     return from_hip(apm::xor_launch(L, (hipStream_t)stream));
 }

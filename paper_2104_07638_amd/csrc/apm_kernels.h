@@ -106,20 +106,25 @@ struct LaunchXor {
     int32_t* info;
     int32_t batch;
     int n;                     // blocks per matrix
-    void* ws;                  // top-level node matrices, ws_stride elements per matrix
+    void* ws;                  // NAND: top-level node matrices, ws_stride elements per matrix
     int64_t ws_stride;
+    int32_t* flag;             // NAND, where nand_flags() says so: [batch] workspace
     int mode;                  // 0: XOR minors [batch][2^(n+1) - 2]; 1: XNOR [batch][2^n];
                                // 2: NAND [batch][3^n]
 };
 
-// Elements of top-level workspace per matrix with n blocks (0: none needed).
+// Elements of top-level workspace per matrix with n blocks (0: none needed), and whether a flag
+// per matrix is needed as well.
 int64_t xor_ws_elems(int n, int mode);
+bool nand_flags(int n, int mode);
 hipError_t xor_launch(const LaunchXor& L, hipStream_t st);
 // The register kernels (4 blocks and more, no workspace).
 hipError_t xor_row_launch_r64(const LaunchXor& L, hipStream_t st);
 hipError_t xor_row_launch_c128(const LaunchXor& L, hipStream_t st);
 hipError_t xnor_row_launch_r64(const LaunchXor& L, hipStream_t st);
 hipError_t xnor_row_launch_c128(const LaunchXor& L, hipStream_t st);
+hipError_t nand_row_launch_r64(const LaunchXor& L, int32_t* flag, hipStream_t st);
+hipError_t nand_row_launch_c128(const LaunchXor& L, int32_t* flag, hipStream_t st);
 
 // Leading principal minors: [batch][n] of [batch][n][n] (dtype R64 or C128, n <= 32).
 hipError_t lead_launch(int dtype, const void* A, void* out, int32_t* info, int32_t batch, int n, hipStream_t st);

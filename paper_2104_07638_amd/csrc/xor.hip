@@ -22,19 +22,24 @@
 // times the block's determinant).  Only the 2^n leaves are minors of distinct subsets;
 // they are written in block-mask order (bit i <-> block i kept).
 //
+// Which kernel: XOR and XNOR minors of 4 blocks and more run in xor_row.h, NAND minors of
+// kNandRowMin blocks and more in nand_row.h (node matrices in registers).  Here are the XOR and
+// XNOR minors of up to 3 blocks (a matrix is one LDS subtree), the NAND minors of few blocks,
+// and those of the matrices whose pivots need shifts, which nand_row.h flags.
+//
 // Mapping (one wavefront per matrix; lanes exchange through LDS with wavefront syncs only,
 // so the stores of the minors stay in flight):
 //   * the last block is decided first, so a node's remaining blocks are the leading ones
 //     and the pivot rows are the last two rows of its matrix; depth k of the output holds
 //     the minors of the k trailing blocks, and every subtree's outputs are contiguous;
-//   * top levels (d < T = n - Q): depth first over the 2^T depth-T nodes, the stack of
+//   * top levels (NAND, d < T = n - Q): depth first over the 3^T depth-T nodes, the stack of
 //     node matrices (orders 2(n-1) ... 2(n-T+1)) in a workspace in global memory (the
 //     depth T-1 node in LDS), each row of the child split over as many lanes as the
 //     wavefront allows, with the pivot row (scaled by 1/pivot) staged in LDS; the depth-T
 //     node is written straight into LDS;
-//   * the last Q = min(n, 6) levels of each depth-T node: breadth first in LDS, one row of
-//     a child per lane (split over column groups where the rows leave lanes idle), so
-//     each level is one pass (at most 64 rows);
+//   * the last Q = min(n, 4) levels (XOR, XNOR: all of at most 3) of each depth-T node: breadth
+//     first in LDS, one row of a child per lane (split over column groups where the rows leave
+//     lanes idle), so each level is one pass (at most 64 rows);
 //   * the LDS arrays are sized for the one tree a kernel runs (binary or ternary), which
 //     sets how many wavefronts a compute unit holds;
 //   * every size is a compile-time constant (one kernel per number of blocks), so no index
@@ -49,12 +54,12 @@
 namespace apm {
 namespace {
 
-#ifndef APM_XOR_Q
-#define APM_XOR_Q 6
-#endif
-constexpr int kXQ = APM_XOR_Q;   // levels expanded breadth first in LDS (XOR, XNOR)
+// XOR and XNOR: the register kernels (xor_row.h) take over at 4 blocks, the fewest they are
+// built for.  They are not slower there (3000 complex matrices of 4 blocks: 9.8 us against
+// 10.1, launch-bound) and gain from 6 blocks on (3000 complex XNOR of 6: 8.9 against 12.5).
+constexpr int kRowMin = 4;
+constexpr int kXQ = 3;       // levels expanded breadth first in LDS (XOR, XNOR)
 constexpr int kXQ3 = 4;      // the same for the ternary NAND tree
-constexpr int kRowMin = 4;   // XOR and XNOR from here on: xor_row.h
 // modes: the XOR, XNOR and NAND cases of Sec. III
 constexpr int kXor = 0, kXnor = 1, kNand = 2;
 __host__ __device__ constexpr int xq(int mode) { return mode == kNand ? kXQ3 : kXQ; }
@@ -125,10 +130,9 @@ struct XorLds {
     // minors of the nodes of the current and the next level (at most 2^Q, or 3^Q for NAND)
     typename F::E mn[2][MODE == kNand ? pow3(xq(MODE)) : (1 << xq(MODE))];
     typename F::E wk[64];            // subtree levels: each child's pivot row times 1/pivot
-    typename F::E wv[32];            // top levels: pivot row times 1/pivot (XNOR: first row of
-    typename F::E wv2[32];           // the pivot block's inverse times the pivot rows, and second)
+    typename F::E wv[MODE == kNand ? 32 : 1];   // top levels: pivot row times 1/pivot
     typename F::E topm[17];          // minors along the top path
-    typename F::E pre[xpre_need(MODE)];     // the depth T-1 node
+    typename F::E pre[MODE == kNand ? xpre_need(MODE) : 1];     // the depth T-1 node
     // zeros: the pivot column and rows of a child that leaves its block out, so that it
     // runs the keeping children's code
     typename F::E wz[xzero_need(MODE)];
@@ -240,9 +244,9 @@ __device__ __noinline__ int nand_top_slow(const typename F::E* P, typename F::E*
 // Top level D of matrix order 2N: the child of the depth-D node on path s (a group of
 // columns of a row of the child per lane), from the workspace (or the input at D = 0) to
 // the workspace.
-template <class F, int N, int T, int D, int MODE>
-__device__ __forceinline__ void xor_top(int d0, int s, const typename F::E* A0, typename F::E* st,
-                                        typename F::E* ob, XorLds<F, MODE>& sh, double& chk, XPiv& xp)
+template <class F, int N, int T, int D>
+__device__ __forceinline__ void nand_top(int d0, int s, const typename F::E* A0, typename F::E* st,
+                                         XorLds<F, kNand>& sh, double& chk, XPiv& xp)
 {
     if constexpr (D < T) {
         using E = typename F::E;
@@ -255,7 +259,7 @@ __device__ __forceinline__ void xor_top(int d0, int s, const typename F::E* A0, 
             constexpr bool kPinP = kPin && D == T - 1, kLdsC = D == T - 1 || (kPin && D == T - 2);
             constexpr int ps = kPinP ? xs(m) : m;
             constexpr int cs = kLdsC ? xs(mc) : mc;
-            static_assert(!kLdsC || mc * xs(mc) <= (D == T - 1 ? xbuf_need(MODE) : xpre_need(MODE)),
+            static_assert(!kLdsC || mc * xs(mc) <= (D == T - 1 ? xbuf_need(kNand) : xpre_need(kNand)),
                           "LDS node fits its buffer");
             const E* P;
             if constexpr (D == 0) {
@@ -273,9 +277,8 @@ __device__ __forceinline__ void xor_top(int d0, int s, const typename F::E* A0, 
             } else {
                 C = st + xor_top_off(N, D + 1);
             }
-            // this level's choice: a bit (XOR, XNOR) or a ternary digit (NAND: 0 leaves the
-            // block out, 1 and 2 keep its first or second row)
-            const int a = MODE == kNand ? (int)((s / pow3(T - 1 - D)) % 3) : (s >> (T - 1 - D)) & 1;
+            // this level's choice: 0 leaves the block out, 1 and 2 keep its first or second row
+            const int a = (int)((s / pow3(T - 1 - D)) % 3);
             // every load of the node first, then the arithmetic: one round trip per node.
             // Lane h mc + i takes columns [h cw, (h + 1) cw) of row i of the child.
             constexpr int cw = top_cols(mc), H = (mc + cw - 1) / cw;
@@ -288,9 +291,9 @@ __device__ __forceinline__ void xor_top(int d0, int s, const typename F::E* A0, 
                 for (int j = 0; j < cw; ++j)
                     if (kEven || h0 + j < mc) row[j] = P[i * ps + h0 + j];
             }
-            if (MODE == kXor || (MODE == kNand && a != 0)) {
+            if (a != 0) {
                 // child keeps row p of the last block: 1 x 1 pivot
-                const int p = MODE == kNand ? mc + a - 1 : mc + a;
+                const int p = mc + a - 1;
                 const E pv = P[p * ps + p];
                 E pc = F::zero(), pr = F::zero();
                 if (act) pc = P[i * ps + p];
@@ -300,7 +303,6 @@ __device__ __forceinline__ void xor_top(int d0, int s, const typename F::E* A0, 
                 if (lane == 0) {
                     const E mk = F::bmul(sh.topm[D], pv, 0);
                     sh.topm[D + 1] = mk;
-                    if constexpr (MODE == kXor) ob[(int64_t(2) << D) - 2 + (s >> (T - 1 - D))] = mk;
                     chk += F::fincheck(mk);
                 }
                 wave_sync();
@@ -309,63 +311,30 @@ __device__ __forceinline__ void xor_top(int d0, int s, const typename F::E* A0, 
                     for (int j = 0; j < cw; ++j)
                         if (kEven || h0 + j < mc) C[i * cs + h0 + j] = F::upd(row[j], pc, sh.wv[h0 + j]);
                 }
-                if constexpr (MODE == kNand) {
-                    // pivot shift (Sec. II test on the kept row and column of the child's Schur
-                    // complement), checked once the child is written (its inputs are at hand by
-                    // then); a shifted child is formed again and corrected once its subtree is
-                    // complete.  No lane holding an entry kFastExp binary orders above p:
-                    // the test passes without the maxima.
-                    const int ep = xexp(pv);
-                    const int le = max(lane < mc ? xexp(pr) : 0, act ? xexp(pc) : 0);
-                    int code = kNoEv;
-                    if (ballot(ep == 0 || le >= ep + kFastExp)) {
-                        code = nand_top_slow<F, N, D>(P, C, p, ps, cs, sh, xp.tau2, xp.es);
-                        if (code != kNoEv) {
-                            xp.nsh += 1;
-                            xp.top_own = true;
-                        }
+                // pivot shift (Sec. II test on the kept row and column of the child's Schur
+                // complement), checked once the child is written (its inputs are at hand by
+                // then); a shifted child is formed again and corrected once its subtree is
+                // complete.  No lane holding an entry kFastExp binary orders above p:
+                // the test passes without the maxima.
+                const int ep = xexp(pv);
+                const int le = max(lane < mc ? xexp(pr) : 0, act ? xexp(pc) : 0);
+                int code = kNoEv;
+                if (ballot(ep == 0 || le >= ep + kFastExp)) {
+                    code = nand_top_slow<F, N, D>(P, C, p, ps, cs, sh, xp.tau2, xp.es);
+                    if (code != kNoEv) {
+                        xp.nsh += 1;
+                        xp.top_own = true;
                     }
-                    xp.set_tcode(D, code);
                 }
-            } else if (a == 0) {
-                // XNOR or NAND, the block left out: the leading part of the node, minor unchanged
+                xp.set_tcode(D, code);
+            } else {
+                // the block left out: the leading part of the node, minor unchanged
                 if (lane == 0) sh.topm[D + 1] = sh.topm[D];
-                if constexpr (MODE == kNand) xp.set_tcode(D, kNoEv);
+                xp.set_tcode(D, kNoEv);
                 if (act) {
 #pragma unroll
                     for (int j = 0; j < cw; ++j)
                         if (kEven || h0 + j < mc) C[i * cs + h0 + j] = row[j];
-                }
-            } else {
-                // XNOR, the block kept: 2 x 2 pivot block, its inverse applied to the pivot rows
-                const E a00 = P[mc * ps + mc], a01 = P[mc * ps + mc + 1];
-                const E a10 = P[(mc + 1) * ps + mc], a11 = P[(mc + 1) * ps + mc + 1];
-                E pc0 = F::zero(), pc1 = F::zero(), pr0 = F::zero(), pr1 = F::zero();
-                if (act) {
-                    pc0 = P[i * ps + mc];
-                    pc1 = P[i * ps + mc + 1];
-                }
-                if (lane < mc) {
-                    pr0 = P[mc * ps + lane];
-                    pr1 = P[(mc + 1) * ps + lane];
-                }
-                const E det = F::det2(a00, a01, a10, a11);
-                const typename F::R r = F::recip(det);
-                if (lane < mc) {
-                    sh.wv[lane] = F::rowscale(F::upd(F::bmul(pr0, a11, 0), a01, pr1), r);
-                    sh.wv2[lane] = F::rowscale(F::upd(F::bmul(pr1, a00, 0), a10, pr0), r);
-                }
-                if (lane == 0) {
-                    const E mk = F::bmul(sh.topm[D], det, 0);
-                    sh.topm[D + 1] = mk;
-                    chk += F::fincheck(mk);
-                }
-                wave_sync();
-                if (act) {
-#pragma unroll
-                    for (int j = 0; j < cw; ++j)
-                        if (kEven || h0 + j < mc)
-                            C[i * cs + h0 + j] = F::upd(F::upd(row[j], pc0, sh.wv[h0 + j]), pc1, sh.wv2[h0 + j]);
                 }
             }
             if constexpr (kLdsC) {
@@ -374,7 +343,7 @@ __device__ __forceinline__ void xor_top(int d0, int s, const typename F::E* A0, 
                 wave_mem_fence();   // the child is the next level's node (and wv is rewritten)
             }
         }
-        xor_top<F, N, T, D + 1, MODE>(d0, s, A0, st, ob, sh, chk, xp);
+        nand_top<F, N, T, D + 1>(d0, s, A0, st, sh, chk, xp);
     }
 }
 
@@ -672,19 +641,17 @@ __device__ __noinline__ double nand_top_fix(int dlo, int sp, typename F::E* ob, 
     return chk;
 }
 
-// The block minors of matrix blockIdx.x (one wavefront).
+// The block minors of matrix b (one wavefront).
 template <class F, int N, int MODE>
 __device__ __forceinline__ void xor_matrix(const typename F::E* __restrict__ A, typename F::E* __restrict__ out,
-                                           int32_t* __restrict__ info, int32_t batch,
-                                           typename F::E* __restrict__ ws, int64_t ws_stride)
+                                           int32_t* __restrict__ info, int b, typename F::E* __restrict__ ws,
+                                           int64_t ws_stride, XorLds<F, MODE>& sh)
 {
     using E = typename F::E;
     constexpr int Q = N < xq(MODE) ? N : xq(MODE);
     constexpr int T = N - Q;
+    static_assert(MODE == kNand || T == 0, "XOR and XNOR: no top levels");
     constexpr int w = 2 * N;
-    __shared__ XorLds<F, MODE> sh;
-    const int b = blockIdx.x;
-    if (b >= batch) return;
     const int lane = threadIdx.x;
     const E* A0 = A + (int64_t)b * w * w;
     constexpr int64_t nout = MODE == kNand ? pow3(N) : MODE == kXnor ? (int64_t(1) << N) : (int64_t(2) << N) - 2;
@@ -707,24 +674,20 @@ __device__ __forceinline__ void xor_matrix(const typename F::E* __restrict__ A, 
     if constexpr (MODE == kNand) (void)frexp(wave_max(amax), &xp.es);
     if (lane == 0) sh.topm[0] = F::one();
     for (int e = lane; e < xzero_need(MODE); e += 64) sh.wz[e] = F::zero();
-    constexpr int ntop = MODE == kNand ? (int)pow3(T) : 1 << T;
+    constexpr int ntop = (int)pow3(T);
     for (int s = 0; s < ntop; ++s) {
-        // top levels: redo the path below the first choice that changed from s - 1 (the
-        // number of trailing zero digits of s, binary or ternary)
-        int d0 = 0;
-        if (s) {
-            if constexpr (MODE == kNand) {
+        if constexpr (T > 0) {
+            // top levels: redo the path below the first choice that changed from s - 1 (the
+            // number of trailing zero digits of s)
+            int d0 = 0;
+            if (s) {
                 int tz = 0;
                 for (int t = s; t % 3 == 0; t /= 3) ++tz;
                 d0 = T - 1 - tz;
-            } else {
-                d0 = T - 1 - (31 - __clz((unsigned)(s ^ (s - 1))));
+                if (xp.tc0 | xp.tc1) chk += nand_top_fix<F, N, T, Q>(d0, s - 1, ob, xp.tc0, xp.tc1, xp.es);
             }
+            nand_top<F, N, T, 0>(d0, s, A0, st, sh, chk, xp);
         }
-        if constexpr (MODE == kNand && T > 0) {
-            if (s && (xp.tc0 | xp.tc1)) chk += nand_top_fix<F, N, T, Q>(d0, s - 1, ob, xp.tc0, xp.tc1, xp.es);
-        }
-        xor_top<F, N, T, 0, MODE>(d0, s, A0, st, ob, sh, chk, xp);
         // the subtree of depth-T node s, breadth first in LDS
         if constexpr (T == 0) {
             for (int e = lane; e < w * w; e += 64) sh.buf[0][(e / w) * xs(w) + e % w] = A0[e];
@@ -758,22 +721,38 @@ __device__ __forceinline__ void xor_matrix(const typename F::E* __restrict__ A, 
     if (info && lane == 0) info[b] = bad ? -3 : xp.nsh;
 }
 
+// A wavefront per matrix; with `flag`, only the matrices flagged there.
+template <class F, int N, int MODE>
+__device__ __forceinline__ void xor_batch(const typename F::E* __restrict__ A, typename F::E* __restrict__ out,
+                                          int32_t* __restrict__ info, int32_t batch,
+                                          typename F::E* __restrict__ ws, int64_t ws_stride,
+                                          const int32_t* __restrict__ flag)
+{
+    __shared__ XorLds<F, MODE> sh;
+    for (int b = blockIdx.x; b < batch; b += gridDim.x) {
+        if (flag && !flag[b]) continue;
+        xor_matrix<F, N, MODE>(A, out, info, b, ws, ws_stride, sh);
+        wave_sync();
+    }
+}
+
 template <class F, int N, int MODE>
 __global__ __launch_bounds__(64) void xor_kernel(const typename F::E* __restrict__ A, typename F::E* __restrict__ out,
                                                  int32_t* __restrict__ info, int32_t batch,
-                                                 typename F::E* __restrict__ ws, int64_t ws_stride)
+                                                 typename F::E* __restrict__ ws, int64_t ws_stride,
+                                                 const int32_t* __restrict__ flag)
 {
-    xor_matrix<F, N, MODE>(A, out, info, batch, ws, ws_stride);
+    xor_batch<F, N, MODE>(A, out, info, batch, ws, ws_stride, flag);
 }
 
-// fp64: registers capped for four wavefronts per SIMD (the compiler's choice at 14 blocks,
-// 140 registers, holds three); a few spilled registers cost less than the residency gains.
+// fp64: registers capped for four wavefronts per SIMD (the compiler's choice holds three); a
+// few spilled registers cost less than the residency gains.
 template <int N, int MODE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void xor_kernel_r64(
     const double* __restrict__ A, double* __restrict__ out, int32_t* __restrict__ info, int32_t batch,
-    double* __restrict__ ws, int64_t ws_stride)
+    double* __restrict__ ws, int64_t ws_stride, const int32_t* __restrict__ flag)
 {
-    xor_matrix<FR64, N, MODE>(A, out, info, batch, ws, ws_stride);
+    xor_batch<FR64, N, MODE>(A, out, info, batch, ws, ws_stride, flag);
 }
 
 template <class F, int N, int MODE>
@@ -785,25 +764,32 @@ constexpr auto xor_kernel_for()
         return xor_kernel<F, N, MODE>;
 }
 
+// NAND minors from this many blocks on: nand_row.h, and the kernel here for the matrices it flags.
+constexpr int kNandRowMin = 7;
+
 template <class F, int N>
-hipError_t xor_launch_n(const LaunchXor& L, hipStream_t st)
+hipError_t xor_launch_n(const LaunchXor& L, const int32_t* flag, hipStream_t st)
 {
-    if constexpr (N > 16) {
+    if constexpr (N > 13) {
         return hipErrorInvalidValue;
     } else {
-        if (L.n != N) return xor_launch_n<F, N + 1>(L, st);
+        if (L.n != N) return xor_launch_n<F, N + 1>(L, flag, st);
+        // flagged matrices are few: a grid that fills the chip looks through the flags
+        const unsigned grid = flag && L.batch > 2048 ? 2048u : (unsigned)L.batch;
         auto go = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3((unsigned)L.batch), dim3(64), 0, st,
-                               static_cast<const typename F::E*>(L.A), static_cast<typename F::E*>(L.out), L.info,
-                               L.batch, static_cast<typename F::E*>(L.ws), L.ws_stride);
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(64), 0, st, static_cast<const typename F::E*>(L.A),
+                               static_cast<typename F::E*>(L.out), L.info, L.batch, static_cast<typename F::E*>(L.ws),
+                               L.ws_stride, flag);
         };
-        if (L.mode == kXnor) {
-            go(xor_kernel_for<F, N, kXnor>());
-        } else if (L.mode == kNand) {
-            if constexpr (N <= 13) go(xor_kernel_for<F, N, kNand>());
-            else return hipErrorInvalidValue;
+        if (L.mode == kNand) {
+            go(xor_kernel_for<F, N, kNand>());
+        } else if constexpr (N < kRowMin) {
+            if (L.mode == kXnor)
+                go(xor_kernel_for<F, N, kXnor>());
+            else
+                go(xor_kernel_for<F, N, kXor>());
         } else {
-            go(xor_kernel_for<F, N, kXor>());
+            return hipErrorInvalidValue;
         }
         return hipGetLastError();
     }
@@ -813,21 +799,29 @@ hipError_t xor_launch_n(const LaunchXor& L, hipStream_t st)
 
 int64_t xor_ws_elems(int n, int mode)
 {
+    if (mode != kNand) return 0;
     // depths 1 .. G live in the workspace, the deeper top nodes in LDS
     const int T = n > xq(mode) ? n - xq(mode) : 0;
     const int G = (APM_XOR_PRE && T >= 2) ? T - 2 : T - 1;
     return G >= 1 ? xor_top_off(n, G + 1) : 0;
 }
 
+bool nand_flags(int n, int mode) { return mode == kNand && n >= kNandRowMin; }
+
 hipError_t xor_launch(const LaunchXor& L, hipStream_t st)
 {
+    if (L.dtype != 0 && L.dtype != 2) return hipErrorInvalidValue;
     if (L.mode != kNand && L.n >= kRowMin) {
         if (L.mode == kXor) return L.dtype == 0 ? xor_row_launch_r64(L, st) : xor_row_launch_c128(L, st);
         return L.dtype == 0 ? xnor_row_launch_r64(L, st) : xnor_row_launch_c128(L, st);
     }
-    if (L.dtype == 0) return xor_launch_n<FR64, 1>(L, st);
-    if (L.dtype == 2) return xor_launch_n<FC128, 1>(L, st);
-    return hipErrorInvalidValue;
+    const int32_t* flag = nullptr;
+    if (nand_flags(L.n, L.mode)) {
+        const hipError_t e = L.dtype == 0 ? nand_row_launch_r64(L, L.flag, st) : nand_row_launch_c128(L, L.flag, st);
+        if (e != hipSuccess) return e;
+        flag = L.flag;
+    }
+    return L.dtype == 0 ? xor_launch_n<FR64, 1>(L, flag, st) : xor_launch_n<FC128, 1>(L, flag, st);
 }
 
 }  // namespace apm
