@@ -979,9 +979,9 @@ apm_status block_minors(int mode, apm_dtype dt, const void* A, const apm_batch* 
     L.n = bd->n_uniform;
     L.mode = mode;
     L.ws_stride = apm::xor_ws_elems(L.n, mode);
-    if (L.ws_stride > 0) {
-        const size_t nodes = (size_t)L.ws_stride * (size_t)bd->batch * (dt == APM_C128 ? 16 : 8);
-        const size_t flags = apm::nand_flags(L.n, mode) ? (size_t)bd->batch * 4 : 0;
+    const size_t nodes = (size_t)L.ws_stride * (size_t)bd->batch * (dt == APM_C128 ? 16 : 8);
+    const size_t flags = apm::nand_flags(L.n, mode) ? (size_t)bd->batch * 4 : 0;
+    if (nodes + flags > 0) {
         apm_status s = get_xor_ws((hipStream_t)stream, nodes + flags, &L.ws);
         if (s != APM_OK) return s;
         if (flags) L.flag = reinterpret_cast<int32_t*>(static_cast<char*>(L.ws) + nodes);

@@ -54,7 +54,8 @@ struct Unit {
     using R = typename F::R;
     static constexpr int T = N > 8 ? N - 8 : 0;
     static constexpr int R0 = 2 * (N - T);
-    static constexpr int NPH = N >= 8 ? 9 : N == 7 ? 3 : 1;   // order-12 nodes of a unit
+    static_assert(N >= 7, "order 14 at least");
+    static constexpr int NPH = N >= 8 ? 9 : 3;   // order-12 nodes of a unit
 
     Lds<F>& sh;
     int l16;
@@ -483,10 +484,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
         un.template lanes<0>(o[0] ? o[0] + ph * kPhase : nullptr, o[1] ? o[1] + ph * kPhase : nullptr);
         un.template lanes<1>(o[2] ? o[2] + ph * kPhase : nullptr, o[3] ? o[3] + ph * kPhase : nullptr);
     };
+    // whether every unit here has a pivot to shift already: its minors are formed elsewhere
+    auto lost = [&]() {
+        const uint64_t k = un.bad_rows | ballot(!valid);
+        return (k & 0xFFFFull) && (k & 0xFFFF0000ull) && (k & 0xFFFF00000000ull) && (k >> 48);
+    };
     auto below14 = [&](const E(&M14)[14], E mk14) {
         E mkd;
         typename F::R rd;
         un.pivots(M14, mk14, mkd, rd);
+        if (lost()) return;
 #pragma unroll 1
         for (int c2 = 0; c2 < 3; ++c2) {
             E C[12];
@@ -499,13 +506,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
         E mkd, C[14];
         typename F::R rd;
         un.pivots(M, mk, mkd, rd);
-        const E mc = un.choose(c1, M, C, mk, mkd, rd);
-        below14(C, mc);
-    } else if constexpr (N == 7) {
-        below14(M, mk);
+        if (!lost()) {
+            const E mc = un.choose(c1, M, C, mk, mkd, rd);
+            below14(C, mc);
+        }
     } else {
-        un.template node<12>(M, mk, 0);
-        emit(0);
+        below14(M, mk);
     }
     // a pivot to shift: the matrix is done over; else its info
     const bool shift = finite && (((un.bad_rows >> (lane & 48)) & 0xFFFF) || ((un.bad_units >> (lane >> 4)) & 1));

@@ -1,11 +1,11 @@
-// nand_row_c128.hip -- the register NAND minors kernels (nand_row.h), complex128, 6 to 13 blocks.
+// nand_row_c128.hip -- the register NAND minors kernels (nand_row.h), complex128, 7 to 13 blocks.
 #include "nand_row.h"
 
 namespace apm {
 
 hipError_t nand_row_launch_c128(const LaunchXor& L, int32_t* flag, hipStream_t st)
 {
-    return nrow::launch_n<FC128, 1, 6>(L, flag, st);
+    return nrow::launch_n<FC128, 1, 7>(L, flag, st);
 }
 
 }  // namespace apm

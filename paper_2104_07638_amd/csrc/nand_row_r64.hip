@@ -1,11 +1,11 @@
-// nand_row_r64.hip -- the register NAND minors kernels (nand_row.h), fp64, 6 to 13 blocks.
+// nand_row_r64.hip -- the register NAND minors kernels (nand_row.h), fp64, 7 to 13 blocks.
 #include "nand_row.h"
 
 namespace apm {
 
 hipError_t nand_row_launch_r64(const LaunchXor& L, int32_t* flag, hipStream_t st)
 {
-    return nrow::launch_n<FR64, 2, 6>(L, flag, st);
+    return nrow::launch_n<FR64, 2, 7>(L, flag, st);
 }
 
 }  // namespace apm
