@@ -72,8 +72,10 @@ struct McWork {
     uint64_t* draws;   // the step's Philox draws: calls 0 and 1 of every walker, 4 x uint64 each
     uint16_t* feat;
     float* logits;
-    float* dout;
-    float* gbuf;
+    uint32_t* sel;     // training: the output gradient's entries and value per walker,
+    uint16_t* gval;    // the loss's shares and the partial maxima of log|c'|
+    double* lpart;
+    double* maxp;
     void* mlp;
 };
 
@@ -102,8 +104,10 @@ int64_t mc_layout(const apm_mc_model* m, int64_t W, bool with_net, char* base, M
     if (with_net) {
         w.feat = reinterpret_cast<uint16_t*>(take(W * dp * 2));
         w.logits = reinterpret_cast<float*>(take(W * op * 4));
-        w.dout = reinterpret_cast<float*>(take(W * op * 4));
-        w.gbuf = reinterpret_cast<float*>(take(W * 4));
+        w.sel = reinterpret_cast<uint32_t*>(take(W * 4));
+        w.gval = reinterpret_cast<uint16_t*>(take(W * 2));
+        w.lpart = reinterpret_cast<double*>(take(W / 32 * 8));
+        w.maxp = reinterpret_cast<double*>(take(apm::mc_max_parts((int)W) * 8));
         w.mlp = take(apm::mlp_work_bytes(dp, op, (int)W));
     }
     if (wk) *wk = w;
@@ -286,7 +290,7 @@ apm_status apm_mc_accept(const apm_mc_model* m, const apm_mc_chain* ch, uint64_t
         e = apm::mc_accept_launch(a, moved, proposed, logq, wk.csum, wk.minors, summ_of(a, wk),
                                   rec ? rec->logc_prop : nullptr,
                                   rec ? rec->accepted : nullptr, rec ? rec->obs_logw : nullptr,
-                                  rec ? rec->obs_sign : nullptr, st);
+                                  rec ? rec->obs_sign : nullptr, nullptr, st);
     return from_hip(e);
 }
 
@@ -336,12 +340,23 @@ apm_status apm_mc_step(const apm_mc_model* m, const apm_mc_chain* ch, const apm_
     if (e == hipSuccess)
         e = apm::mc_accept_launch(a, moved, prop, logq, wk.csum, wk.minors, summ_of(a, wk), logc,
                                   rec ? rec->accepted : nullptr,
-                                  rec ? rec->obs_logw : nullptr, rec ? rec->obs_sign : nullptr, st);
+                                  rec ? rec->obs_logw : nullptr, rec ? rec->obs_sign : nullptr,
+                                  train ? wk.maxp : nullptr, st);
     if (train) {
-        if (e == hipSuccess)
-            e = apm::mc_loss_launch(a, wk.logits, op, prop, logc, wk.gbuf, wk.dout, rec ? rec->loss : nullptr, kClip,
-                                    st);
-        if (e == hipSuccess) e = apm::mlp_backward_launch(nt, wk.dout, W, mw, st);
+        apm::MlpPick pk{};
+        pk.logits = wk.logits;
+        pk.prop = prop;
+        pk.logc = logc;
+        pk.maxp = wk.maxp;
+        pk.nmax = apm::mc_max_parts(W);
+        pk.L2 = m->L * m->L;
+        pk.per_bin = m->n_tau / m->n_bin;
+        pk.clip = kClip;
+        pk.sel = wk.sel;
+        pk.g = wk.gval;
+        pk.lpart = wk.lpart;
+        pk.loss = rec ? rec->loss : nullptr;
+        if (e == hipSuccess) e = apm::mlp_backward_picked_launch(nt, pk, W, mw, st);
         if (e == hipSuccess)
             e = apm::mlp_adam_launch(nt, true, train->lr, train->beta1, train->beta2, train->eps, train->t, st);
     }

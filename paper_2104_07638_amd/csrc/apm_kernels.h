@@ -154,6 +154,23 @@ MlpWork mlp_work_carve(void* work, int dp, int op, int B);
 hipError_t mlp_forward_launch(const MlpNet& net, const uint16_t* x, int B, float* out, const MlpWork* wk,
                               hipStream_t st);
 hipError_t mlp_backward_launch(const MlpNet& net, const float* dout, int B, const MlpWork& wk, hipStream_t st);
+
+// The output gradient of the Monte Carlo regression (two entries a row), formed in the backward
+// pass from the step's logits, proposals and weights.
+struct MlpPick {
+    const float* logits;       // [B][Op]
+    const uint32_t* prop;      // [B] proposed vertices
+    const double* logc;        // [B] log|c'|
+    const double* maxp;        // [nmax] partial maxima of the finite ones (-inf: none)
+    int nmax;
+    int L2, per_bin;           // sites; time points per bin
+    double clip;
+    uint32_t* sel;             // workspace [B]: the entries of a row, in the low and the high half
+    uint16_t* g;               // workspace [B]: their value, BF16
+    double* lpart;             // workspace [B / 32]: shares of the loss
+    float* loss;               // [1] or NULL
+};
+hipError_t mlp_backward_picked_launch(const MlpNet& net, const MlpPick& pk, int B, const MlpWork& wk, hipStream_t st);
 hipError_t mlp_adam_launch(const MlpNet& net, bool update, float lr, float b1, float b2, float eps, int t,
                            hipStream_t st);
 
@@ -184,13 +201,15 @@ hipError_t mc_propose_launch(const McArgs& a, const int32_t* moved, int32_t* mov
                              int stride, uint32_t* prop, double* logq, double* mats, hipStream_t st);
 hipError_t mc_gather_launch(const McArgs& a, double* mats, hipStream_t st);
 // summ (if not NULL): per-walker (c[V], d[V]) written by the connected-sum kernel; else
-// c[V] and d[V] are formed from the full c[] and minors arrays.
+// c[V] and d[V] are formed from the full c[] and minors arrays.  maxp (if not NULL): receives
+// the partial maxima of mc_max_launch.
 hipError_t mc_accept_launch(const McArgs& a, const int32_t* moved, const uint32_t* prop, const double* logq,
                             const double* c, const double* minors, const double* summ, double* logc_out,
-                            uint8_t* acc_out, float* obs_logw, int8_t* obs_sign, hipStream_t st);
+                            uint8_t* acc_out, float* obs_logw, int8_t* obs_sign, double* maxp, hipStream_t st);
 hipError_t mc_set_launch(const McArgs& a, const double* c, const double* minors, const double* summ,
                          hipStream_t st);
-hipError_t mc_loss_launch(const McArgs& a, const float* logits, int Op, const uint32_t* prop, const double* logc,
-                          float* gbuf, float* dout, float* loss, double clip, hipStream_t st);
+// Partial maxima of the finite log|c'| of a batch, for mlp_backward_picked_launch: 256 walkers each.
+int mc_max_parts(int W);
+hipError_t mc_max_launch(int W, const double* logc, double* maxp, hipStream_t st);
 
 }  // namespace apm

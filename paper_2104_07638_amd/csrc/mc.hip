@@ -479,16 +479,31 @@ __global__ __launch_bounds__(256) void mc_accept_kernel(McArgs a, const int32_t*
     accept_one(a, w, wt, moved, prop, logq, logc_out, acc_out, obs_logw, obs_sign);
 }
 
+// The largest finite value of the workgroup (256 threads) to maxp[blockIdx.x].
+__device__ __forceinline__ void block_max(double y, double* __restrict__ maxp)
+{
+    __shared__ double red[4];
+    const double mx = wave_max_d(isfinite(y) ? y : -INFINITY);
+    if (lane_id() == 0) red[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) maxp[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+}
+
 // one lane per walker, with (c[V], d[V]) per walker from the connected-sum kernel
 __global__ __launch_bounds__(256) void mc_accept_summ_kernel(McArgs a, const int32_t* __restrict__ moved,
                                                              const uint32_t* __restrict__ prop,
                                                              const double* __restrict__ logq,
                                                              const double* __restrict__ summ, double* logc_out,
-                                                             uint8_t* acc_out, float* obs_logw, int8_t* obs_sign)
+                                                             uint8_t* acc_out, float* obs_logw, int8_t* obs_sign,
+                                                             double* __restrict__ maxp)
 {
     const int w = blockIdx.x * 256 + threadIdx.x;
-    if (w >= a.W) return;
-    accept_one(a, w, summ_weight(a, w, summ), moved, prop, logq, logc_out, acc_out, obs_logw, obs_sign);
+    Wt wt{-INFINITY, 0};
+    if (w < a.W) {
+        wt = summ_weight(a, w, summ);
+        accept_one(a, w, wt, moved, prop, logq, logc_out, acc_out, obs_logw, obs_sign);
+    }
+    if (maxp) block_max(wt.lc, maxp);
 }
 
 __global__ __launch_bounds__(256) void mc_set_kernel(McArgs a, const double* __restrict__ c,
@@ -504,63 +519,11 @@ __global__ __launch_bounds__(256) void mc_set_kernel(McArgs a, const double* __r
     }
 }
 
-// Regression targets: y = log|c'| clipped below at (max - clip); g[r] = 2 (pred - y) / W.
-__global__ __launch_bounds__(1024) void mc_loss_kernel(McArgs a, const float* __restrict__ logits, int Op,
-                                                       const uint32_t* __restrict__ prop,
-                                                       const double* __restrict__ logc, float* __restrict__ gbuf,
-                                                       float* loss, double clip)
+// Largest finite log|c'| of 256 walkers (-inf: none).
+__global__ __launch_bounds__(256) void mc_max_kernel(int W, const double* __restrict__ logc, double* __restrict__ maxp)
 {
-    __shared__ double red[1024 / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int L2 = a.L * a.L, per_bin = a.n_tau / a.n_bin;
-    double mx = -INFINITY;
-    for (int r = tid; r < a.W; r += 1024) {
-        const double y = logc[r];
-        if (isfinite(y)) mx = fmax(mx, y);
-    }
-    mx = wave_max(mx);
-    if (lane == 0) red[wv] = mx;
-    __syncthreads();
-    mx = -INFINITY;
-    for (int i = 0; i < 16; ++i) mx = fmax(mx, red[i]);
-    __syncthreads();
-    const bool any = mx > -INFINITY;
-    const double floor_y = mx - clip;
-    double sum = 0.0;
-    for (int r = tid; r < a.W; r += 1024) {
-        float gr = 0.0f;
-        if (any) {
-            double y = logc[r];
-            y = isfinite(y) ? fmax(y, floor_y) : floor_y;
-            const uint32_t v = prop[r];
-            const int s = (int)(v & 0xFFFFu), b = (int)(v >> 16) / per_bin;
-            const double pred = (double)logits[(size_t)r * Op + s] + (double)logits[(size_t)r * Op + L2 + b];
-            const double diff = pred - y;
-            gr = (float)(2.0 * diff / a.W);
-            sum += diff * diff;
-        }
-        gbuf[r] = gr;
-    }
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-    if (lane == 0) red[wv] = sum;
-    __syncthreads();
-    if (tid == 0 && loss) {
-        double s = 0.0;
-        for (int i = 0; i < 16; ++i) s += red[i];
-        loss[0] = (float)(s / (a.W > 0 ? a.W : 1));
-    }
-}
-
-__global__ __launch_bounds__(256) void mc_dout_kernel(McArgs a, int Op, const uint32_t* __restrict__ prop,
-                                                      const float* __restrict__ gbuf, float* __restrict__ dout)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)a.W * Op) return;
-    const int r = (int)(i / Op), f = (int)(i % Op);
-    const uint32_t v = prop[r];
-    const int L2 = a.L * a.L;
-    const int s = (int)(v & 0xFFFFu), b = (int)(v >> 16) / (a.n_tau / a.n_bin);
-    dout[i] = (f == s || f == L2 + b) ? gbuf[r] : 0.0f;
+    const int w = blockIdx.x * 256 + threadIdx.x;
+    block_max(w < W ? logc[w] : -INFINITY, maxp);
 }
 
 unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
@@ -598,15 +561,25 @@ hipError_t mc_gather_launch(const McArgs& a, double* mats, hipStream_t st)
 
 hipError_t mc_accept_launch(const McArgs& a, const int32_t* moved, const uint32_t* prop, const double* logq,
                             const double* c, const double* minors, const double* summ, double* logc_out,
-                            uint8_t* acc_out, float* obs_logw, int8_t* obs_sign, hipStream_t st)
+                            uint8_t* acc_out, float* obs_logw, int8_t* obs_sign, double* maxp, hipStream_t st)
 {
     if (a.W == 0) return hipSuccess;
-    if (summ)
+    if (summ) {
         hipLaunchKernelGGL(mc_accept_summ_kernel, dim3(blocks_for(a.W, 256)), dim3(256), 0, st, a, moved, prop, logq,
-                           summ, logc_out, acc_out, obs_logw, obs_sign);
-    else
-        hipLaunchKernelGGL(mc_accept_kernel, dim3(blocks_for(a.W, 4)), dim3(256), 0, st, a, moved, prop, logq, c,
-                           minors, logc_out, acc_out, obs_logw, obs_sign);
+                           summ, logc_out, acc_out, obs_logw, obs_sign, maxp);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(mc_accept_kernel, dim3(blocks_for(a.W, 4)), dim3(256), 0, st, a, moved, prop, logq, c, minors,
+                       logc_out, acc_out, obs_logw, obs_sign);
+    return maxp ? mc_max_launch(a.W, logc_out, maxp, st) : hipGetLastError();
+}
+
+int mc_max_parts(int W) { return (int)blocks_for(W, 256); }
+
+hipError_t mc_max_launch(int W, const double* logc, double* maxp, hipStream_t st)
+{
+    if (W == 0) return hipSuccess;
+    hipLaunchKernelGGL(mc_max_kernel, dim3(blocks_for(W, 256)), dim3(256), 0, st, W, logc, maxp);
     return hipGetLastError();
 }
 
@@ -614,16 +587,6 @@ hipError_t mc_set_launch(const McArgs& a, const double* c, const double* minors,
 {
     if (a.W == 0) return hipSuccess;
     hipLaunchKernelGGL(mc_set_kernel, dim3(blocks_for(a.W, 4)), dim3(256), 0, st, a, c, minors, summ);
-    return hipGetLastError();
-}
-
-hipError_t mc_loss_launch(const McArgs& a, const float* logits, int Op, const uint32_t* prop, const double* logc,
-                          float* gbuf, float* dout, float* loss, double clip, hipStream_t st)
-{
-    if (a.W == 0) return hipSuccess;
-    hipLaunchKernelGGL(mc_loss_kernel, dim3(1), dim3(1024), 0, st, a, logits, Op, prop, logc, gbuf, loss, clip);
-    hipLaunchKernelGGL(mc_dout_kernel, dim3(blocks_for((int64_t)a.W * Op, 256)), dim3(256), 0, st, a, Op, prop, gbuf,
-                       dout);
     return hipGetLastError();
 }
 

@@ -18,11 +18,13 @@
 //
 // Backward: the hidden gradients are chained the same way through the transposed
 // weights (W^T kept as a second BF16 copy); the weight gradients dW = dZ^T H sum over
-// the batch, one wavefront per 16 x 16 tile of dW with the batch as the K dimension,
-// from BF16 copies of dZ and H stored feature-major ([feature][batch]).
+// the batch as the K dimension, from BF16 copies of dZ and H in the operand order of
+// those products (store_t).  The Monte Carlo training step passes its output gradient in picked form
+// (two entries a row, MlpPick), computed in the backward kernel itself.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "apm_kernels.h"
 
@@ -66,11 +68,35 @@ __device__ __forceinline__ v4f mfma(v4s a, v4s b, v4f c)
 
 __device__ __forceinline__ v4s ld4(const uint16_t* p) { return *reinterpret_cast<const v4s*>(p); }
 
-// store the 4 values a lane holds for (features f0..f0+3, batch row r) feature-major
-__device__ __forceinline__ void store_t(uint16_t* dst, int B, int f0, int r, v4s v)
+// Batch-contiguous copies (of activations and gradients, for the weight gradients) are kept in
+// the operand order of products over the batch: 16 features x 32 rows are 64 lanes x 8 values,
+// lane 16 (row % 16 / 4) + feature holding rows 4 (lane / 16) .. + 3 of the first 16 rows and
+// then of the second, one such block after the other.  A load of both operands of a step is then
+// 1024 consecutive bytes; in
+// plain feature-major rows (2 B bytes apart, a power of two at the usual batches) the 16 lines
+// of a load fell on one L2 channel.
+//
+// Store tile (ft, rt) from the layout of a D tile (lane 16 g + r: features 4 g .. 4 g + 3 of row
+// r): transpose 4 x 4 values within each four lanes, then one 8-byte store.
+__device__ __forceinline__ void store_t(uint16_t* dst, int B, int ft, int rt, v4s v)
 {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) dst[(size_t)(f0 + j) * B + r] = (uint16_t)v[j];
+    const int lane = threadIdx.x & 63, q = lane & 3;
+    const uint2 p = __builtin_bit_cast(uint2, v);      // features (0, 1) and (2, 3)
+    const bool hi = q & 2, odd = q & 1;
+    // lanes q and q ^ 2 exchange a word: own features (q & 2) + {0, 1} of rows q and q ^ 2
+    const uint32_t mine = hi ? p.y : p.x;
+    const uint32_t far = (uint32_t)__builtin_amdgcn_mov_dpp((int)(hi ? p.x : p.y), 0x4E, 0xF, 0xF, true);
+    // lanes q and q ^ 1 exchange both: own feature q of rows (q, q ^ 1) and (q ^ 2, q ^ 3)
+    const uint32_t mine1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)mine, 0xB1, 0xF, 0xF, true);
+    const uint32_t far1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)far, 0xB1, 0xF, 0xF, true);
+    // the halves of the even and the odd row of each pair: low ones in even lanes, high in odd
+    const uint32_t sel = odd ? 0x07060302u : 0x05040100u;
+    const uint32_t a = __builtin_amdgcn_perm(odd ? mine : mine1, odd ? mine1 : mine, sel);
+    const uint32_t b = __builtin_amdgcn_perm(odd ? far : far1, odd ? far1 : far, sel);
+    const uint2 o = hi ? make_uint2(b, a) : make_uint2(a, b);
+    // feature 4 g + q, rows 4 (r / 4) .. + 3
+    const int at = ((lane & 15) >> 2) * 16 + 4 * (lane >> 4) + q;
+    *reinterpret_cast<uint2*>(dst + ((size_t)ft * (B / 32) + (rt >> 1)) * 512 + at * 8 + 4 * (rt & 1)) = o;
 }
 
 // Forward pass: one workgroup of kFwdWaves wavefronts per 32 batch rows.  The wavefronts
@@ -147,7 +173,7 @@ __device__ __forceinline__ void hidden_slice(const v4s (&a)[kMtPerWave][KS], con
             act_out[(mt * 2 + nt) * 64 + lane] = hb;
             const int r = row0 + 16 * nt + r16;
             if (save) *reinterpret_cast<v4f*>(save + (size_t)r * H + f0) = h;
-            if (save_t) store_t(save_t, B, f0, r, hb);
+            if (save_t) store_t(save_t, B, mt, row0 / 16 + nt, hb);
         }
     }
 }
@@ -193,11 +219,11 @@ __global__ __launch_bounds__(64 * kFwdWaves) void mlp_fwd_kernel(const uint16_t*
         load_tile<8>(W3, t, w3[u]);
         bb3[u] = *reinterpret_cast<const v4f*>(b3 + 16 * t + 4 * g);
     }
-    if (actT && wv == 0) {   // training: feature-major BF16 copy of the input
+    if (actT && wv == 0) {   // training: batch-contiguous copy of the input
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-            for (int ks = 0; ks < KS1; ++ks) store_t(actT, B, 16 * ks + 4 * g, row0 + 16 * nt + r16, xo[nt][ks]);
+            for (int ks = 0; ks < KS1; ++ks) store_t(actT, B, ks, row0 / 16 + nt, xo[nt][ks]);
     }
     hidden_slice<KS1>(w1, bb1, xo, kMtPerWave * wv, act1, row0, B, h1s, actT ? actT + (size_t)DP * B : nullptr);
     __syncthreads();
@@ -239,130 +265,346 @@ __global__ __launch_bounds__(64 * kFwdWaves) void mlp_fwd_kernel(const uint16_t*
     }
 }
 
-// dz2 = (W3^T dout^T) * (1 - h2^2), dz1 = (W2^T dz2^T) * (1 - h1^2); BF16 feature-major
-// copies of dout, dz2 and dz1 go to gT = [Op | H | H][B].
-__global__ __launch_bounds__(64) void mlp_bwd_act_kernel(const uint16_t* __restrict__ wt, int DP, int Op,
-                                                         const float* __restrict__ dout, int B,
-                                                         const float* __restrict__ h1s,
-                                                         const float* __restrict__ h2s, uint16_t* __restrict__ gT)
+// The gradient of the Monte Carlo regression at the outputs of row r: two entries, the proposed
+// site's logit and the proposed bin's, hold the same value g[r]; all others are zero.
+//   pred = site logit + bin logit, y = log|c'| clipped below at (batch maximum - clip),
+//   g = 2 (pred - y) / B; the loss is the mean of (pred - y)^2.
+// One thread per row of the workgroup's 32; the maximum from the acceptance kernel's partial
+// ones.  Writes the rows' entries for the weight gradients and the workgroup's share of the
+// loss, and leaves them in LDS for the hidden gradients.
+struct Picked {
+    uint32_t sel[32];    // entries: low and high half
+    float g[32];         // rounded to BF16
+};
+
+__device__ __forceinline__ void pick_rows(const MlpPick& pk, int Op, int B, int row0, Picked& lds)
 {
-    const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
-    const int row0 = blockIdx.x * 32;
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
+        double mx = -INFINITY;
+        for (int i = lane; i < pk.nmax; i += 64) mx = fmax(mx, pk.maxp[i]);
+        for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+        double sq = 0.0;
+        if (lane < 32) {
+            const int r = row0 + lane;
+            const uint32_t v = pk.prop[r];
+            const int f1 = (int)(v & 0xFFFFu), f2 = pk.L2 + (int)(v >> 16) / pk.per_bin;
+            float g = 0.0f;
+            if (mx > -INFINITY) {
+                const double floor_y = mx - pk.clip;
+                double y = pk.logc[r];
+                y = isfinite(y) ? fmax(y, floor_y) : floor_y;
+                const double pred = (double)pk.logits[(size_t)r * Op + f1] + (double)pk.logits[(size_t)r * Op + f2];
+                const double diff = pred - y;
+                g = (float)(2.0 * diff / B);
+                sq = diff * diff;
+            }
+            const uint32_t sel = (uint32_t)f1 | ((uint32_t)f2 << 16);
+            const uint16_t gb = f2bf(g);
+            lds.sel[lane] = sel;
+            lds.g[lane] = bf2f((short)gb);
+            pk.sel[r] = sel;
+            pk.g[r] = gb;
+        }
+        for (int o = 16; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+        if (lane == 0) pk.lpart[blockIdx.x] = sq;
+    }
+    __syncthreads();
+}
+
+// dz2 = (W3^T dout^T) * (1 - h2^2), dz1 = (W2^T dz2^T) * (1 - h1^2); batch-contiguous
+// BF16 copies (store_t) of dout, dz2 and dz1 go to gT = [Op | H | H][B].  One workgroup of four wavefronts per 32
+// rows; wavefront v computes the hidden tiles 2 v and 2 v + 1 of both gradients, dz2 passed on
+// through LDS in B-operand order.  Picks: the output gradient has two entries a row
+// (pick_rows), so W3^T dout^T is two rows of W3 times g (8-byte pieces of the operand-ordered
+// copy, the same sum), and neither dout nor its copy is formed.
+// Measured at 8192 rows (272 outputs): one wavefront per 32 rows with dense dout 18.5 us, and
+// 33 us more to form it; now 10 us in all.
+constexpr int kBwdWaves = 4;
+
+template <bool Picks>
+__global__ __launch_bounds__(64 * kBwdWaves) void mlp_bwd_act_kernel(const uint16_t* __restrict__ w,
+                                                                     const uint16_t* __restrict__ wt, int DP, int Op,
+                                                                     const float* __restrict__ dout, MlpPick pk, int B,
+                                                                     const float* __restrict__ h1s,
+                                                                     const float* __restrict__ h2s,
+                                                                     uint16_t* __restrict__ gT)
+{
+    __shared__ v4s dz[8 * 2 * 64];   // [feature tile][row tile][lane]
+    __shared__ Picked pick;
+    const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4, wv = threadIdx.x >> 6;
+    const int row0 = blockIdx.x * 32, mt0 = 2 * wv;
     const uint16_t* W2T = wt + (size_t)H * DP;        // [H][H]
     const uint16_t* W3T = W2T + H * H;                // [H][Op]
     uint16_t* doT = gT;
     uint16_t* dz2T = gT + (size_t)Op * B;
     uint16_t* dz1T = dz2T + (size_t)H * B;
 
-    v4f acc[8][2];
+    // operands that depend on nothing: the transposed W2 rows and the activations
+    v4s w2[2][8];
+    v4f h2[2][2], h1[2][2];
 #pragma unroll
-    for (int mt = 0; mt < 8; ++mt) acc[mt][0] = acc[mt][1] = v4f{0.f, 0.f, 0.f, 0.f};
-    for (int ks = 0; ks < Op / 16; ++ks) {
-        v4s bo[2];
+    for (int m = 0; m < 2; ++m) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w2[m][k] = ld4(W2T + (size_t)(16 * (mt0 + m) + r16) * H + 16 * k + 4 * g);
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
-            const int r = row0 + 16 * nt + r16;
-            bo[nt] = pack_bf(*reinterpret_cast<const v4f*>(dout + (size_t)r * Op + 16 * ks + 4 * g));
-            store_t(doT, B, 16 * ks + 4 * g, r, bo[nt]);
-        }
-#pragma unroll
-        for (int mt = 0; mt < 8; ++mt) {
-            const v4s a = ld4(W3T + (size_t)(16 * mt + r16) * Op + 16 * ks + 4 * g);
-            acc[mt][0] = mfma(a, bo[0], acc[mt][0]);
-            acc[mt][1] = mfma(a, bo[1], acc[mt][1]);
+            const size_t at = (size_t)(row0 + 16 * nt + r16) * H + 16 * (mt0 + m) + 4 * g;
+            h2[m][nt] = *reinterpret_cast<const v4f*>(h2s + at);
+            h1[m][nt] = *reinterpret_cast<const v4f*>(h1s + at);
         }
     }
-    v4s dz2o[2][8];
-#pragma unroll
-    for (int mt = 0; mt < 8; ++mt)
+    v4f acc[2][2];
+    if constexpr (Picks) {
+        pick_rows(pk, Op, B, row0, pick);
+        const uint16_t* W3 = w + (size_t)H * DP + H * H;   // operand order, K = H
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
-            const int r = row0 + 16 * nt + r16;
-            const int f0 = 16 * mt + 4 * g;
-            const v4f h = *reinterpret_cast<const v4f*>(h2s + (size_t)r * H + f0);
-            const v4f dz = acc[mt][nt] * (1.0f - h * h);
-            dz2o[nt][mt] = pack_bf(dz);
-            store_t(dz2T, B, f0, r, dz2o[nt][mt]);
-        }
+            const uint32_t sel = pick.sel[16 * nt + r16];
+            const float gr = pick.g[16 * nt + r16];
 #pragma unroll
-    for (int mt = 0; mt < 8; ++mt) {
+            for (int m = 0; m < 2; ++m) {
+                // features 16 mt + 4 g .. + 3 of row f: lane 16 g + f % 16 of tile (f / 16, mt)
+                auto piece = [&](uint32_t f) {
+                    return ld4(W3 + ((size_t)((f >> 4) * (H / 16) + mt0 + m) * 64 + 16 * g + (f & 15)) * 4);
+                };
+                const v4s p1 = piece(sel & 0xFFFFu), p2 = piece(sel >> 16);
+                // (the products are exact in fp32: one rounding, as in the matrix product)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[m][nt][j] = fmaf(gr, bf2f(p1[j]), gr * bf2f(p2[j]));
+            }
+        }
+    } else {
+#pragma unroll
+        for (int m = 0; m < 2; ++m) acc[m][0] = acc[m][1] = v4f{0.f, 0.f, 0.f, 0.f};
+        for (int ks = 0; ks < Op / 16; ++ks) {
+            v4s bo[2];
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                const int r = row0 + 16 * nt + r16;
+                bo[nt] = pack_bf(*reinterpret_cast<const v4f*>(dout + (size_t)r * Op + 16 * ks + 4 * g));
+                if ((ks & 3) == wv) store_t(doT, B, ks, row0 / 16 + nt, bo[nt]);
+            }
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                const v4s a = ld4(W3T + (size_t)(16 * (mt0 + m) + r16) * Op + 16 * ks + 4 * g);
+                acc[m][0] = mfma(a, bo[0], acc[m][0]);
+                acc[m][1] = mfma(a, bo[1], acc[m][1]);
+            }
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            const v4f h = h2[m][nt];
+            const v4s d = pack_bf(acc[m][nt] * (1.0f - h * h));
+            dz[((mt0 + m) * 2 + nt) * 64 + lane] = d;
+            store_t(dz2T, B, mt0 + m, row0 / 16 + nt, d);
+        }
+    __syncthreads();
+    v4s b[2][8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) b[nt][k] = dz[(k * 2 + nt) * 64 + lane];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
         v4f a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0;
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            const v4s a = ld4(W2T + (size_t)(16 * mt + r16) * H + 16 * ks + 4 * g);
-            a0 = mfma(a, dz2o[0][ks], a0);
-            a1 = mfma(a, dz2o[1][ks], a1);
+        for (int k = 0; k < 8; ++k) {
+            a0 = mfma(w2[m][k], b[0][k], a0);
+            a1 = mfma(w2[m][k], b[1][k], a1);
         }
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
-            const int r = row0 + 16 * nt + r16;
-            const int f0 = 16 * mt + 4 * g;
-            const v4f h = *reinterpret_cast<const v4f*>(h1s + (size_t)r * H + f0);
-            const v4f dz = (nt == 0 ? a0 : a1) * (1.0f - h * h);
-            store_t(dz1T, B, f0, r, pack_bf(dz));
+            const v4f h = h1[m][nt];
+            store_t(dz1T, B, mt0 + m, row0 / 16 + nt, pack_bf((nt == 0 ? a0 : a1) * (1.0f - h * h)));
         }
     }
 }
 
-// dW[f][k] = sum_r dZ[r][f] act[r][k] and db[f] = sum_r dZ[r][f], one 16 x 16 tile of dW per
-// wavefront.  Tiles: layer 3 (Op/16 x 8), then layer 2 (8 x 8), then layer 1 (8 x DP/16).
-__global__ __launch_bounds__(64) void mlp_wgrad_kernel(const uint16_t* __restrict__ gT,
-                                                       const uint16_t* __restrict__ actT, int B, int DP, int Op,
-                                                       float* __restrict__ grad)
+// dW[f][k] = sum_r dZ[r][f] act[r][k] and db[f] = sum_r dZ[r][f].  A wavefront sums one 16 x 16
+// tile of dW over the whole batch, 32 rows a step in two chains of products (rows 0..15 and
+// 16..31 of each step), so the order of the sums does not depend on the launch.  Four tiles of
+// one row of tiles share a workgroup and its A operands: the batch goes by in blocks of 16
+// steps, each wavefront brings four steps of A to LDS (two buffers, one barrier a block) and
+// loads its own B operands, both two blocks ahead.  Row tiles: layer 3 (Op/16, two workgroups each),
+// layer 2 (8, two each), layer 1 (8).  Picks: layer 3's A is formed from the rows' two entries; an
+// extra workgroup adds up the loss.
+// Bound by the latency of the loads: with a step's loads issued at its start (one wavefront a
+// workgroup, nothing shared) 8192 rows took 84 us.
+constexpr int kGradWaves = 4, kGradSteps = 16;
+
+template <bool Picks>
+__global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu(1, 1))) void mlp_wgrad_kernel(const uint16_t* __restrict__ gT,
+                                                                    const uint16_t* __restrict__ actT, MlpPick pk,
+                                                                    int B, int DP, int Op, float* __restrict__ grad)
 {
-    const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
-    const int T3 = (Op / 16) * 8;
+    constexpr int kOwn = kGradSteps / kGradWaves;   // steps of A a wavefront brings in
+    __shared__ uint4 As[2][kGradSteps][64];
+    const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4, wv = threadIdx.x >> 6;
+    const int T3 = (Op / 16) * 2;
     int t = blockIdx.x;
+    if constexpr (Picks) {
+        if (t == T3 + 16 + 8) {
+            // the loss: the backward kernel's shares, one per 32 rows
+            double sum = 0.0;
+            for (int i = threadIdx.x; i < B / 32; i += 64 * kGradWaves) sum += pk.lpart[i];
+            for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+            double* red = reinterpret_cast<double*>(&As[0][0][0]);
+            if (lane == 0) red[wv] = sum;
+            __syncthreads();
+            if (threadIdx.x == 0) pk.loss[0] = (float)(((red[0] + red[1]) + (red[2] + red[3])) / B);
+            return;
+        }
+    }
     const uint16_t* A;     // dZ^T [f][B]
     const uint16_t* Bm;    // act^T [k][B]
     float* dW;
     float* db;
     int ld, it, kt;
+    bool picked = false;
     float* bias = grad + (size_t)H * DP + H * H + (size_t)Op * H;
     if (t < T3) {
-        it = t / 8;
-        kt = t % 8;
+        it = t / 2;
+        kt = 4 * (t % 2) + wv;
         A = gT;
         Bm = actT + (size_t)(DP + H) * B;
         dW = grad + (size_t)H * DP + H * H;
         ld = H;
         db = bias + 2 * H;
-    } else if (t < T3 + 64) {
+        picked = Picks;
+    } else if (t < T3 + 16) {
         t -= T3;
-        it = t / 8;
-        kt = t % 8;
+        it = t / 2;
+        kt = 4 * (t % 2) + wv;
         A = gT + (size_t)Op * B;
         Bm = actT + (size_t)DP * B;
         dW = grad + (size_t)H * DP;
         ld = H;
         db = bias + H;
     } else {
-        t -= T3 + 64;
-        const int kt1 = DP / 16;
-        it = t / kt1;
-        kt = t % kt1;
+        it = t - T3 - 16;
+        kt = wv;
         A = gT + (size_t)(Op + H) * B;
         Bm = actT;
         dW = grad;
         ld = DP;
         db = bias;
     }
-    const uint16_t* pa = A + (size_t)(16 * it + r16) * B + 4 * g;
-    const uint16_t* pb = Bm + (size_t)(16 * kt + r16) * B + 4 * g;
+    const bool act = 16 * kt < ld;              // (layer 1 may have fewer tiles than wavefronts)
+    const int steps = B / 32;
+    const uint16_t* pa = A + (size_t)it * B * 16 + lane * 8;
+    const uint16_t* pb = Bm + (size_t)(act ? kt : 0) * B * 16 + lane * 8;
     v4f c0 = {0.f, 0.f, 0.f, 0.f}, c1 = c0;
     float bs = 0.f;
-    for (int r0 = 0; r0 < B; r0 += 32) {
-        const v4s a0 = ld4(pa + r0), b0 = ld4(pb + r0);
-        const v4s a1 = ld4(pa + r0 + 16), b1 = ld4(pb + r0 + 16);
-        c0 = mfma(a0, b0, c0);
-        c1 = mfma(a1, b1, c1);
-        if (kt == 0)
-            bs += (bf2f(a0[0]) + bf2f(a0[1])) + (bf2f(a0[2]) + bf2f(a0[3])) + (bf2f(a1[0]) + bf2f(a1[1])) +
-                  (bf2f(a1[2]) + bf2f(a1[3]));
-    }
-    const v4f c = c0 + c1;
+    auto run = [&](auto is_picked) {
+        constexpr bool kPicked = decltype(is_picked)::value;
+        // operands of two blocks of steps in flight (past the end: the last step's, A taken as
+        // zeros): this wavefront's share of A, and B.  Picks: A is a block of zeros in which each
+        // thread sets the entries of two rows, and clears them when the buffer comes round again.
+        constexpr int kRows = 32 * kGradSteps / (64 * kGradWaves);   // rows of a block per thread
+        uint4 an[2][kPicked ? 1 : kOwn];
+        uint32_t sn[2][kPicked ? kRows : 1];
+        uint16_t gn[2][kPicked ? kRows : 1];
+        int set[2][kPicked ? 2 * kRows : 1];       // entries set in each buffer (-1: none)
+        uint4 bn[2][kGradSteps];
+        auto load_a = [&](int s0, int p) {
+            if constexpr (kPicked) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) dW[(size_t)(16 * it + 4 * g + j) * ld + 16 * kt + r16] = c[j];
+                for (int i = 0; i < kRows; ++i) {
+                    const int r = min(32 * s0 + (int)threadIdx.x + 64 * kGradWaves * i, B - 1);
+                    sn[p][i] = pk.sel[r];
+                    gn[p][i] = pk.g[r];
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < kOwn; ++i)
+                    an[p][i] = *reinterpret_cast<const uint4*>(pa + (size_t)min(s0 + kOwn * wv + i, steps - 1) * 512);
+            }
+        };
+        auto load_b = [&](int s0, uint4 (&b)[kGradSteps]) {
+#pragma unroll
+            for (int i = 0; i < kGradSteps; ++i)
+                b[i] = *reinterpret_cast<const uint4*>(pb + (size_t)min(s0 + i, steps - 1) * 512);
+        };
+        auto block = [&](int s0, int p, uint4 (&bn)[kGradSteps]) {
+            uint4 (&lds)[kGradSteps][64] = As[p];
+            if constexpr (kPicked) {
+                uint16_t* e = reinterpret_cast<uint16_t*>(&lds[0][0]);
+#pragma unroll
+                for (int i = 0; i < 2 * kRows; ++i)
+                    if (set[p][i] >= 0) e[set[p][i]] = 0;
+#pragma unroll
+                for (int i = 0; i < kRows; ++i) {
+                    const int q = (int)threadIdx.x + 64 * kGradWaves * i;   // row of the block
+                    // its place but for the feature: step, half, rows of four (see store_t)
+                    const int at = (q >> 5) * 512 + ((q & 15) >> 2) * 128 + ((q >> 4) & 1) * 4 + (q & 3);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const uint32_t f = h ? sn[p][i] >> 16 : sn[p][i] & 0xFFFFu;
+                        const bool in = (int)(f >> 4) == it && 32 * s0 + q < B;
+                        set[p][2 * i + h] = in ? at + (int)(f & 15) * 8 : -1;
+                        if (in) e[set[p][2 * i + h]] = gn[p][i];
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < kOwn; ++i) {
+                    const uint32_t in = s0 + kOwn * wv + i < steps ? ~0u : 0u;
+                    const uint4 w = an[p][i];
+                    lds[kOwn * wv + i][lane] = make_uint4(w.x & in, w.y & in, w.z & in, w.w & in);
+                }
+            }
+            load_a(s0 + 2 * kGradSteps, p);
+            __syncthreads();
+            uint4 a[kGradSteps];
+#pragma unroll
+            for (int i = 0; i < kGradSteps; ++i) a[i] = lds[i][lane];
+            __builtin_amdgcn_sched_barrier(0);   // every read of the block in flight at once
+            auto lo = [](uint4 v) { return __builtin_bit_cast(v4s, make_uint2(v.x, v.y)); };
+            auto hi = [](uint4 v) { return __builtin_bit_cast(v4s, make_uint2(v.z, v.w)); };
+#pragma unroll
+            for (int i = 0; i < kGradSteps; ++i) {
+                c0 = mfma(lo(a[i]), lo(bn[i]), c0);
+                c1 = mfma(hi(a[i]), hi(bn[i]), c1);
+            }
+            load_b(s0 + 2 * kGradSteps, bn);
+            if (kt == 0) {
+#pragma unroll
+                for (int i = 0; i < kGradSteps; ++i) {
+                    const v4s a0 = lo(a[i]), a1 = hi(a[i]);
+                    bs += (bf2f(a0[0]) + bf2f(a0[1])) + (bf2f(a0[2]) + bf2f(a0[3])) + (bf2f(a1[0]) + bf2f(a1[1])) +
+                          (bf2f(a1[2]) + bf2f(a1[3]));
+                }
+            }
+        };
+        load_a(0, 0);
+        load_b(0, bn[0]);
+        load_a(kGradSteps, 1);
+        load_b(kGradSteps, bn[1]);
+        if constexpr (kPicked) {
+#pragma unroll
+            for (int i = 0; i < 2 * kRows; ++i) set[0][i] = set[1][i] = -1;
+            for (int i = threadIdx.x; i < 2 * kGradSteps * 64; i += 64 * kGradWaves)
+                (&As[0][0][0])[i] = make_uint4(0, 0, 0, 0);
+            __syncthreads();
+        }
+        for (int s0 = 0; s0 < steps; s0 += 2 * kGradSteps) {
+            block(s0, 0, bn[0]);
+            block(s0 + kGradSteps, 1, bn[1]);
+        }
+    };
+    if (picked)
+        run(std::integral_constant<bool, Picks>{});
+    else
+        run(std::integral_constant<bool, false>{});
+    const v4f c = c0 + c1;
+    if (act) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) dW[(size_t)(16 * it + 4 * g + j) * ld + 16 * kt + r16] = c[j];
+    }
     if (kt == 0) {
         bs += __shfl_xor(bs, 16);
         bs += __shfl_xor(bs, 32);
@@ -457,15 +699,30 @@ hipError_t mlp_forward_launch(const MlpNet& net, const uint16_t* x, int B, float
     return hipGetLastError();
 }
 
-hipError_t mlp_backward_launch(const MlpNet& net, const float* dout, int B, const MlpWork& wk, hipStream_t st)
+namespace {
+
+template <bool Picks>
+hipError_t backward(const MlpNet& net, const float* dout, const MlpPick& pk, int B, const MlpWork& wk, hipStream_t st)
 {
     if (B == 0) return hipSuccess;
-    hipLaunchKernelGGL(mlp_bwd_act_kernel, dim3((unsigned)(B / 32)), dim3(64), 0, st, net.wt, net.dp, net.op, dout, B,
-                       wk.h1, wk.h2, wk.gT);
-    const int tiles = (net.op / 16) * 8 + 64 + 8 * (net.dp / 16);
-    hipLaunchKernelGGL(mlp_wgrad_kernel, dim3((unsigned)tiles), dim3(64), 0, st, wk.gT, wk.actT, B, net.dp, net.op,
-                       net.grad);
+    hipLaunchKernelGGL(mlp_bwd_act_kernel<Picks>, dim3((unsigned)(B / 32)), dim3(64 * kBwdWaves), 0, st, net.w, net.wt,
+                       net.dp, net.op, dout, pk, B, wk.h1, wk.h2, wk.gT);
+    const int tiles = (net.op / 16) * 2 + 16 + 8;
+    hipLaunchKernelGGL(mlp_wgrad_kernel<Picks>, dim3((unsigned)(tiles + (Picks && pk.loss ? 1 : 0))),
+                       dim3(64 * kGradWaves), 0, st, wk.gT, wk.actT, pk, B, net.dp, net.op, net.grad);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t mlp_backward_launch(const MlpNet& net, const float* dout, int B, const MlpWork& wk, hipStream_t st)
+{
+    return backward<false>(net, dout, MlpPick{}, B, wk, st);
+}
+
+hipError_t mlp_backward_picked_launch(const MlpNet& net, const MlpPick& pk, int B, const MlpWork& wk, hipStream_t st)
+{
+    return backward<true>(net, nullptr, pk, B, wk, st);
 }
 
 hipError_t mlp_adam_launch(const MlpNet& net, bool update, float lr, float b1, float b2, float eps, int t,
