@@ -297,6 +297,43 @@ __device__ __forceinline__ void row_child(cd& c0, cd& c1, cd& c2, cd& c3, cd a0,
         : "v"(a0.x), "v"(a0.y), "v"(a1.x), "v"(a1.y), "v"(a2.x), "v"(a2.y), "v"(a3.x), "v"(a3.y), "v"(w.x), "v"(w.y), "n"(P));
 }
 
+// a[r] -= (lane P of s[r]) w, with sources other than the results
+template <int P>
+__device__ __forceinline__ void row_sub(double& a0, double& a1, double& a2, double& a3, double s0, double s1, double s2, double s3, double w)
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, -%4, %8" APM_BC(9)
+        "v_fmac_f64_dpp %1, -%5, %8" APM_BC(9)
+        "v_fmac_f64_dpp %2, -%6, %8" APM_BC(9)
+        "v_fmac_f64_dpp %3, -%7, %8" APM_BC(9)
+        : "+&v"(a0), "+&v"(a1), "+&v"(a2), "+&v"(a3)
+        : "v"(s0), "v"(s1), "v"(s2), "v"(s3), "v"(w), "n"(P));
+}
+
+template <int P>
+__device__ __forceinline__ void row_sub(cd& a0, cd& a1, cd& a2, cd& a3, cd s0, cd s1, cd s2, cd s3, cd w)
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %9, %17" APM_BC(18)
+        "v_fmac_f64_dpp %2, %11, %17" APM_BC(18)
+        "v_fmac_f64_dpp %4, %13, %17" APM_BC(18)
+        "v_fmac_f64_dpp %6, %15, %17" APM_BC(18)
+        "v_fmac_f64_dpp %1, -%9, %16" APM_BC(18)
+        "v_fmac_f64_dpp %3, -%11, %16" APM_BC(18)
+        "v_fmac_f64_dpp %5, -%13, %16" APM_BC(18)
+        "v_fmac_f64_dpp %7, -%15, %16" APM_BC(18)
+        "v_fmac_f64_dpp %0, -%8, %16" APM_BC(18)
+        "v_fmac_f64_dpp %2, -%10, %16" APM_BC(18)
+        "v_fmac_f64_dpp %4, -%12, %16" APM_BC(18)
+        "v_fmac_f64_dpp %6, -%14, %16" APM_BC(18)
+        "v_fmac_f64_dpp %1, -%8, %17" APM_BC(18)
+        "v_fmac_f64_dpp %3, -%10, %17" APM_BC(18)
+        "v_fmac_f64_dpp %5, -%12, %17" APM_BC(18)
+        "v_fmac_f64_dpp %7, -%14, %17" APM_BC(18)
+        : "+&v"(a0.x), "+&v"(a0.y), "+&v"(a1.x), "+&v"(a1.y), "+&v"(a2.x), "+&v"(a2.y), "+&v"(a3.x), "+&v"(a3.y)
+        : "v"(s0.x), "v"(s0.y), "v"(s1.x), "v"(s1.y), "v"(s2.x), "v"(s2.y), "v"(s3.x), "v"(s3.y), "v"(w.x), "v"(w.y), "n"(P));
+}
+
 // c[r] = a[r] - (lane P of a[r]) w0 - (lane P + 1 of a[r]) w1
 template <int P>
 __device__ __forceinline__ void row_child2(double& c0, double& c1, double a0, double a1, double w0, double w1)
