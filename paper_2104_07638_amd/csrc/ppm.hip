@@ -15,8 +15,8 @@
 // (Orders below 12 use fewer L1 indices, see PermPlan.)
 // A lane runs Th over all of H in Gray order (row sums updated one index at a time), and
 // for each Th adds prod_{i in S} (+-r_i) into acc[Sh] for every Sh containing Th: the
-// factor of the L1 and L2 indices is one product per Th, the H indices are a depth-first
-// superset tree whose leaves are fused multiply-adds.  The lanes of one Sl1 (2^|Sl1| of
+// factor of the L1 and L2 indices is one product per Th, the H indices are products of two
+// halves of the superset (supersets()), one fused multiply-add each.  The lanes of one Sl1 (2^|Sl1| of
 // them, aligned, never crossing a wavefront) are summed through LDS at the end, and every
 // output is written exactly once: no atomics, no per-T LDS traffic.
 #include <hip/hip_runtime.h>
@@ -28,9 +28,6 @@
 namespace apm {
 namespace {
 
-#ifndef APM_PPM_SCHED_BARRIER
-#define APM_PPM_SCHED_BARRIER 0   // 1: fence each Gray step off from the scheduler (measured slower)
-#endif
 #ifndef APM_PPM_NH
 #define APM_PPM_NH 6   // largest H group: 2^NH fp64 accumulators per lane
 #endif
@@ -93,39 +90,79 @@ constexpr PairTable make_pairs()
 
 __constant__ PairTable kPairs = make_pairs();
 
-// Superset tree of Th over the H indices.  Node S (a superset of TH) has the value
-// parent * f with f = nr[b] = -r_b for the index b just added; a node with children forms its
-// value, a leaf adds parent * f with one fused multiply-add (in place: no sign modifier).
-template <int NH, int TH, int S, int B>
-__device__ __forceinline__ void children(double (&acc)[1 << NH], const double* r, double v);
+// The supersets of Th over the H indices: the k indices outside Th are split into an outer half
+// and an inner half; v[o] is the root times the factors nr[b] = -r_b of the outer subset o (one
+// product each), q[i] the product of the factors of the inner subset i, and every superset is
+// then one multiply-add acc += v[o] q[i].  That is 2^k + 2^(k/2) + 2^(k - k/2) - 2 - (k - k/2)
+// instructions, 14.0 on average over Th for six indices; a depth-first tree, one product and one
+// sum at every inner node, takes 16.1.
 
-template <int NH, int TH, int S, int B>
-constexpr bool has_children()
+// The i-th (from 0) index outside TH.
+template <int NH, int TH>
+constexpr int free_index(int i)
 {
-    for (int b = B; b < NH; ++b)
-        if (!((TH >> b) & 1)) return true;
-    return false;
+    for (int b = 0; b < NH; ++b)
+        if (!((TH >> b) & 1) && i-- == 0) return b;
+    return -1;
 }
 
-template <int NH, int TH, int S, int B>
-__device__ __forceinline__ void visit(double (&acc)[1 << NH], const double* r, double pv, double f)
+// The indices of subset m of the free indices lo, lo + 1, ...
+template <int NH, int TH>
+constexpr int free_set(int lo, int m)
 {
-    if constexpr (has_children<NH, TH, S, B>()) {
-        const double v = pv * f;
-        acc[S] += v;
-        children<NH, TH, S, B>(acc, r, v);
-    } else {
-        acc[S] = fma(pv, f, acc[S]);
+    int r = 0;
+    for (int i = 0; m >> i; ++i)
+        if ((m >> i) & 1) r |= 1 << free_index<NH, TH>(lo + i);
+    return r;
+}
+
+template <int NH, int TH, int KI, int M>
+__device__ __forceinline__ void inner_products(double (&q)[1 << KI], const double* r)
+{
+    if constexpr (M < (1 << KI)) {
+        constexpr int top = 31 - __builtin_clz(M), rest = M & ~(1 << top);
+        if constexpr (rest == 0)
+            q[M] = r[free_index<NH, TH>(top)];
+        else
+            q[M] = q[rest] * r[free_index<NH, TH>(top)];
+        inner_products<NH, TH, KI, M + 1>(q, r);
     }
 }
 
-template <int NH, int TH, int S, int B>
-__device__ __forceinline__ void children(double (&acc)[1 << NH], const double* r, double v)
+template <int NH, int TH, int KI, int KO, int M>
+__device__ __forceinline__ void outer_products(double (&v)[1 << KO], const double* r)
 {
-    if constexpr (B < NH) {
-        if constexpr (!((TH >> B) & 1)) visit<NH, TH, (S | (1 << B)), B + 1>(acc, r, v, r[B]);
-        children<NH, TH, S, B + 1>(acc, r, v);
+    if constexpr (M < (1 << KO)) {
+        constexpr int top = 31 - __builtin_clz(M);
+        v[M] = v[M & ~(1 << top)] * r[free_index<NH, TH>(KI + top)];
+        outer_products<NH, TH, KI, KO, M + 1>(v, r);
     }
+}
+
+template <int NH, int TH, int KI, int KO, int O, int I>
+__device__ __forceinline__ void add_supersets(double (&acc)[1 << NH], const double (&v)[1 << KO],
+                                              const double (&q)[1 << KI])
+{
+    if constexpr (O < (1 << KO)) {
+        constexpr int S = TH | free_set<NH, TH>(0, I) | free_set<NH, TH>(KI, O);
+        if constexpr (I == 0)
+            acc[S] += v[O];
+        else
+            acc[S] = fma(v[O], q[I], acc[S]);
+        constexpr bool wrap = I + 1 == (1 << KI);
+        add_supersets<NH, TH, KI, KO, wrap ? O + 1 : O, wrap ? 0 : I + 1>(acc, v, q);
+    }
+}
+
+template <int NH, int TH>
+__device__ __forceinline__ void supersets(double (&acc)[1 << NH], const double* r, double root)
+{
+    constexpr int K = NH - __builtin_popcount(TH), KO = K / 2, KI = K - KO;
+    double v[1 << KO], q[1 << KI];
+    v[0] = root;
+    outer_products<NH, TH, KI, KO, 1>(v, r);
+    inner_products<NH, TH, KI, 1>(q, r);
+    add_supersets<NH, TH, KI, KO, 0, 0>(acc, v, q);
 }
 
 // Row j of A, read where it is used: the pointer passes through an empty asm so that the
@@ -164,7 +201,7 @@ __device__ __forceinline__ double prod_bits(const double (&v)[NV])
 // Th = G ^ (G >> 1) for G = 0 .. 2^NH - 1.  The sums run over the transpose
 // (r_i(T) = sum_{j in T} A_ji, and per(M) = per(M^T)), so a toggled index j adds one
 // contiguous row of A.
-//   nr[i]  -r_i(T) for the H indices (the tree's factors; the root's sign is compile-time);
+//   nr[i]  -r_i(T) for the H indices (the supersets' factors; the root's sign is compile-time);
 //   q[i]   the factor of an L index i: s_i r_i(T) with s_i = +1 (i in T) or -1 (i in S \ T),
 //          and 1 for i outside S.  With ms[i] = s_i (0 outside S) every update is the exact
 //          fma(+-ms[i], a, q[i]), and the L part of the product is a plain product of q.
@@ -176,9 +213,6 @@ __device__ __forceinline__ void gray_steps(const double* __restrict__ Am, double
 {
     if constexpr (G < (1 << NH)) {
         constexpr int TH = G ^ (G >> 1);
-#if APM_PPM_SCHED_BARRIER
-        __builtin_amdgcn_sched_barrier(0);
-#endif
         if constexpr (G > 0) {
             constexpr bool added = (TH >> __builtin_ctz(G)) & 1;
             double row[N];
@@ -190,24 +224,24 @@ __device__ __forceinline__ void gray_steps(const double* __restrict__ Am, double
         }
         constexpr int NLa = NL > 0 ? NL : 1;
         const double pl = NL > 0 ? prod_bits<(1 << NL) - 1, 0, NLa, NLa>(q) : 1.0;
-        if constexpr (TH == 0) {
-            acc[0] += pl;
-            children<NH, 0, 0, 0>(acc, nr, pl);
-        } else {
-            // root = pl * prod_{i in TH} r_i = (-1)^|TH| pl * prod nr_i; the highest factor
-            // goes through visit()
-            constexpr int top = 31 - __builtin_clz(TH);
-            constexpr int rest = TH & ~(1 << top);
-            double pv = (__builtin_popcount(TH) & 1) ? -pl : pl;
-            if constexpr (rest != 0) pv *= prod_bits<rest, 0, NH, NH>(nr);
-            visit<NH, TH, TH, 0>(acc, nr, pv, nr[top]);
+        // root = pl * prod_{i in TH} r_i = (-1)^|TH| pl * prod nr_i
+        double root = pl;
+        if constexpr (TH != 0) {
+            root = prod_bits<TH, 0, NH, (NH > 0 ? NH : 1)>(nr);
+            root = (__builtin_popcount(TH) & 1) ? -pl * root : pl * root;
         }
+        supersets<NH, TH>(acc, nr, root);
         gray_steps<N, NH, NL, G + 1>(Am, nr, q, acc, ms);
     }
 }
 
+// Bound by fp64 issue: 78% of the vector cycles are busy at order 12, 3000 instructions per
+// wavefront for 729 x 64 pairs of row sums (12), L product (5) and supersets (14) per Gray step.
+// Two wavefronts per SIMD are asked for: without it the compiler overlaps the steps of orders
+// 10 to 12 until they need 270 registers, and runs one (2048 x 12: 305 us; with it 185, the
+// depth-first supersets before 196).  Three spill: 268 us.
 template <int N>
-__global__ __launch_bounds__(64) void ppm_kernel(const double* __restrict__ A, double* __restrict__ out,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ppm_kernel(const double* __restrict__ A, double* __restrict__ out,
                                                  int32_t batch, int32_t b0, int n_uniform,
                                                  const int32_t* __restrict__ nv, const int64_t* __restrict__ in_off,
                                                  const int64_t* __restrict__ out_off)
