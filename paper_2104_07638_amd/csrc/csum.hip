@@ -444,6 +444,149 @@ constexpr RankTables make_rank_tables()
 __constant__ RankTables kRank = make_rank_tables();
 
 
+// Problems of one wavefront and one block (at most 10 bits) have a fixed schedule: for every rank
+// r >= 1 its rows, G lanes a row (the G of rank_pass), and each lane's pairs step by step.  The
+// LDS offsets of a pair's two rows are one table entry per step and lane (c' row in the low
+// half, b row in the high half), loaded once at the start of the problem, so a step is its LDS
+// reads and multiply-adds; computing Yh and the offsets from the lane number took twice the
+// instructions of the multiply-adds.  A lane without a pair in a step reads a row of zeros.  The
+// pairs, and so the sums, are those of rank_pass in the same order.
+template <int M>
+struct OneWave {
+    using CP = CsPlan<M>;
+    static constexpr int H = CP::H, W = 1 << CP::LB, ROW = 8 * (W + 2);   // bytes of a row
+    static constexpr int ZERO = CP::ROWS * ROW;                          // the row of zeros
+    static constexpr int rows(int r)
+    {
+        int c = 1;
+        for (int i = 0; i < r; ++i) c = c * (H - i) / (i + 1);
+        return c;
+    }
+    static constexpr int items(int r) { return (1 << r) - 1; }
+    static constexpr int lanes(int r)
+    {
+        int g = 1;
+        while (g * 2 <= kWave && rows(r) * g * APM_CS_GMUL_SMALL <= kWave && g * 2 <= (items(r) > 0 ? items(r) : 1)) g *= 2;
+        return g;
+    }
+    static constexpr int steps(int r) { return (items(r) + lanes(r) - 1) / lanes(r); }
+    static constexpr int first(int r)
+    {
+        int s = 0;
+        for (int i = 1; i < r; ++i) s += steps(i);
+        return s;
+    }
+    static constexpr int total = first(H + 1);
+    struct Table {
+        uint32_t pair[total > 0 ? total : 1][kWave];
+        uint16_t row[H + 1][kWave];      // offset of the lane's row, 0xFFFF: none
+    };
+    static constexpr Table make()
+    {
+        Table t{};
+        for (int r = 0; r <= H; ++r) {
+            int o = 0;
+            const int g = lanes(r);
+            for (int l = 0; l < kWave; ++l) {
+                t.row[r][l] = 0xFFFF;
+                for (int k = 0; r > 0 && k < steps(r); ++k) t.pair[first(r) + k][l] = (uint32_t)ZERO | ((uint32_t)ZERO << 16);
+            }
+            for (int x = 0; x < (1 << H); ++x) {
+                if (cx_bits(x) != r) continue;
+                // the lowest log2(g) bits of x take the bits of the lane in the group
+                int low[8] = {}, hi = x, nl = 0;
+                for (int q = 1; q < g; q <<= 1) {
+                    low[nl++] = hi & -hi;
+                    hi &= hi - 1;
+                }
+                for (int s = 0; s < g; ++s) {
+                    int ys = 0;
+                    for (int q = 0; q < nl; ++q)
+                        if ((s >> q) & 1) ys |= low[q];
+                    t.row[r][o * g + s] = (uint16_t)(x * ROW);
+                    int z = 0;
+                    for (int k = 0; r > 0 && k < steps(r); ++k, z = (z - hi) & hi) {
+                        if (s + g * k >= items(r)) continue;
+                        const int y = ys | z;
+                        t.pair[first(r) + k][o * g + s] = (uint32_t)(y * ROW) | ((uint32_t)((x ^ y) * ROW) << 16);
+                    }
+                }
+                ++o;
+            }
+        }
+        return t;
+    }
+    static constexpr int cx_bits(int x)
+    {
+        int c = 0;
+        for (; x; x &= x - 1) ++c;
+        return c;
+    }
+};
+
+constexpr int kOneWaveMin = 6;     // fewer bits: a handful of rows, the general passes
+template <int M>
+constexpr bool one_wave() { return M >= kOneWaveMin && cs_threads<M>() == kWave && CsPlan<M>::TB == 0 && kPad; }
+
+template <int M>
+__constant__ typename OneWave<M>::Table kOneWave = OneWave<M>::make();
+
+template <int W>
+__device__ __forceinline__ void ld_row_at(const double* buf, uint32_t off, double (&v)[W])
+{
+#pragma unroll
+    for (int p = 0; p < W / 2; ++p) {
+        const double2 t = *reinterpret_cast<const double2*>(reinterpret_cast<const char*>(buf) + off + 16 * p);
+        v[2 * p] = t.x;
+        v[2 * p + 1] = t.y;
+    }
+}
+
+// Ranks R .. H of the triangular solve in place on the c' block.
+template <int M, int R, int TOT>
+__device__ __forceinline__ void one_wave_ranks(const uint32_t (&pair)[TOT], const uint32_t (&row)[OneWave<M>::H + 1],
+                                               double* cb, const double* bb)
+{
+    using OW = OneWave<M>;
+    constexpr int LB = CsPlan<M>::LB, W = OW::W;
+    if constexpr (R <= OW::H) {
+        double acc[W];
+#pragma unroll
+        for (int i = 0; i < W; ++i) acc[i] = 0.0;
+        if constexpr (R > 0) {
+#pragma unroll
+            for (int k = 0; k < OW::steps(R); ++k) {
+                const uint32_t e = pair[OW::first(R) + k];
+                double f[W], g[W];
+                ld_row_at<W>(cb, e & 0xFFFFu, f);
+                ld_row_at<W>(bb, e >> 16, g);
+                // the products in the order of conv_rows_split (the same sums)
+                conv_half<LB - 1>(reinterpret_cast<const double(&)[W / 2]>(f), reinterpret_cast<const double(&)[W / 2]>(g), acc);
+                conv_half<LB - 1>(reinterpret_cast<const double(&)[W / 2]>(f),
+                                  reinterpret_cast<const double(&)[W / 2]>(g[W / 2]), acc + W / 2);
+                conv_half<LB - 1>(reinterpret_cast<const double(&)[W / 2]>(f[W / 2]),
+                                  reinterpret_cast<const double(&)[W / 2]>(g), acc + W / 2);
+            }
+            group_sum<W>(acc, OW::lanes(R));
+        }
+        constexpr int G = OW::lanes(R);
+        if (row[R] != 0xFFFFu && ((int)threadIdx.x & (G - 1)) == G - 1) {
+            double rr[W], g0[W];
+            ld_row_at<W>(cb, row[R], rr);
+            ld_row_at<W>(bb, 0, g0);
+#pragma unroll
+            for (int i = 0; i < W; ++i) rr[i] += acc[i];
+            tri_tile<LB>(rr, g0);
+#pragma unroll
+            for (int p = 0; p < W / 2; ++p)
+                *reinterpret_cast<double2*>(reinterpret_cast<char*>(cb) + row[R] + 16 * p) =
+                    make_double2(rr[2 * p], rr[2 * p + 1]);
+        }
+        __syncthreads();
+        one_wave_ranks<M, R + 1>(pair, row, cb, bb);
+    }
+}
+
 // Problem (matrix b, root j): solve (*) for the m = n-1-j vertices above j, with NT lanes
 // (tid in [0, NT)).  act = false runs the same passes and barriers without touching memory.
 template <int M, int NT>
@@ -463,8 +606,22 @@ __device__ void cs_problem(const CsArgs& g, int64_t base, int j, bool zero_even,
     double* rhs = kInPlace ? lds_c : lds_r;
 
     static_assert(H < 8, "rank tables cover rows of up to 7 bits");
-    for (int i = tid; i < (1 << H); i += NT) rk_tab[i] = kRank.tab[H][i];
-    if (tid <= H + 1) rk_off[tid] = kRank.off[H][tid];
+    constexpr bool kFixed = one_wave<M>() && NT == kWave;
+    constexpr int kSteps = kFixed ? OneWave<M>::total : 1, kRanks = kFixed ? H + 1 : 1;
+    uint32_t pair[kSteps], row[kRanks];
+    if constexpr (kFixed) {
+#pragma unroll
+        for (int k = 0; k < kSteps; ++k) pair[k] = kOneWave<M>.pair[k][tid];
+#pragma unroll
+        for (int r = 0; r < kRanks; ++r) row[r] = kOneWave<M>.row[r][tid];
+        if (tid < (1 << LB)) {
+            lds_c[OneWave<M>::ZERO / 8 + tid] = 0.0;
+            lds_b[OneWave<M>::ZERO / 8 + tid] = 0.0;
+        }
+    } else {
+        for (int i = tid; i < (1 << H); i += NT) rk_tab[i] = kRank.tab[H][i];
+        if (tid <= H + 1) rk_off[tid] = kRank.off[H][tid];
+    }
     // rooted problem in one block: a0[x] = a[2x + 1] and b[x] = a[2x] are neighbours, so
     // one 16-byte load per x stages both (the block's own b is staged later otherwise)
     constexpr bool kOneBlock = CP::TB == 0;
@@ -535,9 +692,13 @@ __device__ void cs_problem(const CsArgs& g, int64_t base, int j, bool zero_even,
         }
         // a[V] for the summary (the in-place solve overwrites it)
         const double a_full = (CP::TB == 0 && g.summ) ? rhs[sw<LB, kRPad>((1 << P) - 1)] : 0.0;
-        for (int r = 0; r <= H; ++r) {
-            rank_pass<M, NT, true, kRPad>(tid, r, rk_tab, rk_off, lds_c, lds_b, rhs, lds_c);
-            __syncthreads();
+        if constexpr (kFixed) {
+            one_wave_ranks<M, 0>(pair, row, lds_c, lds_b);
+        } else {
+            for (int r = 0; r <= H; ++r) {
+                rank_pass<M, NT, true, kRPad>(tid, r, rk_tab, rk_off, lds_c, lds_b, rhs, lds_c);
+                __syncthreads();
+            }
         }
         if constexpr (CP::TB == 0) {
             if (g.summ) {
@@ -609,8 +770,10 @@ template <int M>
 __global__ __launch_bounds__(cs_threads<M>()) void cs_kernel(CsArgs g, CsMap mp)
 {
     using CP = CsPlan<M>;
-    __shared__ __align__(16) double lds_c[block_len<CP::P, CP::LB, kPad>()];
-    __shared__ __align__(16) double lds_b[block_len<CP::P, CP::LB, kPad>()];
+    // (one row more for the fixed schedules' row of zeros)
+    constexpr int kZeroRow = one_wave<M>() ? (1 << CP::LB) + 2 : 0;
+    __shared__ __align__(16) double lds_c[block_len<CP::P, CP::LB, kPad>() + kZeroRow];
+    __shared__ __align__(16) double lds_b[block_len<CP::P, CP::LB, kPad>() + kZeroRow];
     // problems of one block solve in place in the c' block: no separate right-hand side
     __shared__ __align__(16) double lds_r[CP::TB == 0 ? 2 : block_len<CP::P, CP::LB, false>()];
     __shared__ uint16_t rk_tab[1 << CsPlan<M>::H];
