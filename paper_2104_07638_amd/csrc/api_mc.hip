@@ -160,6 +160,7 @@ hipError_t weights(const apm::McArgs& a, const McWork& wk, hipStream_t st)
     // up to 12 vertices the rooted recursion fits one LDS block: the kernel then writes only
     // c[V] and its rounding scale d[V] per walker instead of the whole c[] array
     C.summ = summ_of(a, wk);
+    C.walkers = true;
     return apm::cs_launch(C, st);
 }
 

@@ -82,6 +82,7 @@ struct LaunchCS {
     uint32_t mode;
     double* summ;              // rooted, orders <= 12 only: (c[V], d[V]) per matrix instead of c[]
     const int32_t* order;      // mixed orders: matrix indices by decreasing order (queue preparation), or NULL
+    bool walkers;              // Monte Carlo weights (one order, rooted, squares of m_up): fixed order of the sums
 };
 
 hipError_t cs_launch(const LaunchCS& L, hipStream_t st);
