@@ -392,47 +392,59 @@ __device__ void cs_problem(const CsArgs& g, int64_t base, int j, bool zero_even,
     }
 }
 
-// Problem p of a launch: matrix b (through the size-sorted queue order when given) and root j.
+// The problems of a launch: matrix b (through the size-sorted queue order when given) with the
+// roots j0 .. j0 + roots - 1.
 struct CsMap {
     int32_t batch;
     int n_uniform;
     const int32_t* nv;
     const int64_t* off;
     const int32_t* order;   // mixed-order rooted batches: matrix indices by decreasing order, else NULL
-    int roots;
+    int j0, roots;
+    bool rooted;            // rooted mode: also c[S] = 0 for the sets without vertex 0
 };
-
-__device__ __forceinline__ bool cs_locate(const CsMap& mp, int64_t p, int m_want, int* b_out, int* j_out,
-                                          int64_t* base_out)
-{
-    if (p >= (int64_t)mp.batch * mp.roots) return false;
-    int b = (int)(p / mp.roots);
-    const int j = (int)(p % mp.roots);
-    if (mp.order) b = mp.order[b];
-    const int n = mp.n_uniform > 0 ? mp.n_uniform : mp.nv[b];
-    if (n - 1 - j != m_want) return false;   // problems with exactly m_want bits
-    *b_out = b;
-    *j_out = j;
-    *base_out = mp.off ? mp.off[b] : ((int64_t)b << n);
-    return true;
-}
 
 #include "csum_blocks.h"
 #include "csum_walk.h"
 
-// One problem per workgroup of one wavefront.
-template <int M>
+// One problem per workgroup of one wavefront: those of LO to HI bits (the workgroups of others
+// end).  One order: a kernel for each number of bits.  Several: a launch that few problems of it
+// fill costs 4.7 us, so 0 to 7 bits, 8 and 9 (twice the registers, four times the LDS) and 10
+// share one each.
+template <int LO, int HI>
+constexpr int cs_len()
+{
+    if constexpr (LO > HI) {
+        return 0;
+    } else {
+        return CsPlan<LO>::LEN > cs_len<LO + 1, HI>() ? CsPlan<LO>::LEN : cs_len<LO + 1, HI>();
+    }
+}
+
+template <int M, int HI>
+__device__ __forceinline__ void cs_dispatch(int m, const CsArgs& g, int64_t base, int j, bool rooted, double* lds_c, double* lds_b)
+{
+    if constexpr (M <= HI) {
+        if (m == M) return cs_problem<M>(g, base, j, rooted, lds_c, lds_b);
+        cs_dispatch<M + 1, HI>(m, g, base, j, rooted, lds_c, lds_b);
+    }
+}
+
+template <int LO, int HI>
 __global__ __launch_bounds__(kWave) void cs_kernel(CsArgs g, CsMap mp)
 {
-    __shared__ __align__(16) double lds_c[CsPlan<M>::LEN];
-    __shared__ __align__(16) double lds_b[CsPlan<M>::LEN];
-    int b = 0, j = 0;
-    int64_t base = 0;
-    if (!cs_locate(mp, blockIdx.x, M, &b, &j, &base)) return;
-    // the rooted problem also writes c[S] = 0 for the sets without vertex 0
+    __shared__ __align__(16) double lds_c[cs_len<LO, HI>()];
+    __shared__ __align__(16) double lds_b[cs_len<LO, HI>()];
+    int b = (int)(blockIdx.x / (unsigned)mp.roots);
+    const int j = mp.j0 + (int)(blockIdx.x - (unsigned)b * (unsigned)mp.roots);
+    if (mp.order) b = mp.order[b];
+    const int n = mp.n_uniform > 0 ? mp.n_uniform : mp.nv[b];
+    const int m = n - 1 - j;
+    if (m < LO || m > HI) return;
+    const int64_t base = mp.off ? mp.off[b] : ((int64_t)b << n);
     CsArgs gb = g;
     if (gb.summ) gb.summ += 2 * (int64_t)b;
-    cs_problem<M>(gb, base, j, mp.roots == 1, lds_c, lds_b);
+    cs_dispatch<LO, HI>(m, gb, base, j, mp.rooted, lds_c, lds_b);
 }
 
 // Every problem of 11 bits or more in one launch, largest first, so that the shorter problems
@@ -450,7 +462,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5
     const int m = n - 1 - j;
     if (m < kBlockBits) return;
     const int64_t base = mp.off ? mp.off[b] : ((int64_t)b << n);
-    block_problem<K>(g, base, j, m, mp.roots == 1, lds_c, lds_b);
+    block_problem<K>(g, base, j, m, mp.rooted, lds_c, lds_b);
 }
 
 template <BlockWeights K>
@@ -460,26 +472,27 @@ hipError_t launch_blocks(int64_t problems, const CsArgs& g, const CsMap& mp, hip
     return hipGetLastError();
 }
 
-template <int M>
-hipError_t launch_m(CsArgs g, const CsMap& mp, hipStream_t st)
+// The problems of LO to HI bits of a launch; all modes, orders up to nmax.
+template <int LO, int HI>
+hipError_t launch_range(const CsArgs& g, CsMap mp, int nmax, hipStream_t st)
 {
-    const int64_t problems = (int64_t)mp.batch * mp.roots;
-    hipLaunchKernelGGL(cs_kernel<M>, dim3((unsigned)problems), dim3(kWave), 0, st, g, mp);
+    if (!mp.rooted) {
+        mp.j0 = mp.n_uniform > 0 && nmax - 1 > HI ? nmax - 1 - HI : 0;
+        mp.roots = nmax - LO - mp.j0;
+        if (mp.roots <= 0) return hipSuccess;
+    }
+    hipLaunchKernelGGL((cs_kernel<LO, HI>), dim3((unsigned)((int64_t)mp.batch * mp.roots)), dim3(kWave), 0, st, g, mp);
     return hipGetLastError();
 }
 
 template <int M>
-hipError_t launch_all_m(int mlo, int mhi, CsArgs g, const CsMap& mp, hipStream_t st)
+hipError_t launch_one(int m, const CsArgs& g, const CsMap& mp, hipStream_t st)
 {
-    if constexpr (M < 0) {
-        return hipSuccess;
-    } else {
-        if (M >= mlo && M <= mhi) {
-            hipError_t e = launch_m<M>(g, mp, st);
-            if (e != hipSuccess) return e;
-        }
-        return launch_all_m<M - 1>(mlo, mhi, g, mp, st);
+    if constexpr (M < kBlockBits) {
+        if (m == M) return launch_range<M, M>(g, mp, M + 1, st);
+        return launch_one<M + 1>(m, g, mp, st);
     }
+    return hipSuccess;
 }
 
 }  // namespace
@@ -489,28 +502,26 @@ hipError_t cs_launch(const LaunchCS& L, hipStream_t st)
     CsArgs g{L.m_up, L.m_dn, L.c, (L.mode & 2u) ? 1 : 0, L.summ};
     const bool all = (L.mode & 1u) != 0;
     const int nmax = L.n_uniform > 0 ? L.n_uniform : L.n_max;
-    const int nmin = L.n_uniform > 0 ? L.n_uniform : 1;
-    const int roots = all ? nmax : 1;
-    CsMap mp{L.batch, L.n_uniform, L.n, L.off, nullptr, roots};
-    // one launch per problem size m = n-1-j (largest first); each workgroup exits unless its
-    // problem has exactly that size
-    int mhi = nmax - 1;
-    const int mlo = all ? 0 : nmin - 1;
-    if (!all && L.n_uniform <= 0 && L.order) mp.order = L.order;
-    if (L.walkers && mhi >= kBlockBits) {
-        auto k = mhi == kBlockBits ? cs_walk_kernel<true> : cs_walk_kernel<false>;
+    const bool mixed = L.n_uniform <= 0;
+    CsMap mp{L.batch, L.n_uniform, L.n, L.off, !all && mixed ? L.order : nullptr, 0, 1, !all};
+    if (L.walkers && nmax > kBlockBits) {
+        auto k = nmax - 1 == kBlockBits ? cs_walk_kernel<true> : cs_walk_kernel<false>;
         hipLaunchKernelGGL(k, dim3((unsigned)L.batch), dim3(kWalkThreads), 0, st, g, nmax);
         return hipGetLastError();
     }
-    if (mhi >= kBlockBits) {
+    if (nmax > kBlockBits) {
         const int64_t problems = (int64_t)mp.batch * (all ? nmax - kBlockBits : 1);
         const hipError_t e = g.weights ? launch_blocks<kGiven>(problems, g, mp, st)
                              : g.dn    ? launch_blocks<kProduct>(problems, g, mp, st)
                                        : launch_blocks<kSquare>(problems, g, mp, st);
-        if (e != hipSuccess) return e;
-        mhi = kBlockBits - 1;
+        if (e != hipSuccess || (!all && !mixed)) return e;
     }
-    return launch_all_m<kBlockBits - 1>(mlo, mhi, g, mp, st);
+    if (!all && !mixed) return launch_one<0>(nmax - 1, g, mp, st);
+    hipError_t e = hipSuccess;
+    if (nmax > 10) e = launch_range<10, 10>(g, mp, nmax, st);
+    if (e == hipSuccess && nmax > 8) e = launch_range<8, 9>(g, mp, nmax, st);
+    if (e == hipSuccess) e = launch_range<0, 7>(g, mp, nmax, st);
+    return e;
 }
 
 }  // namespace apm
