@@ -322,12 +322,21 @@ def autotune_minors(dtype, n, batch=4096, stream=None):
 
 # ----------------------------------------------------------------- torch wrappers
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# torch.cuda.current_stream() builds a Stream object on each call, 2.8 us of the 8.8 us that a small
+# all_minors call took; the raw handle of the same stream takes 0.2.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:
+        if _raw_stream is not None and _raw_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_raw_device())
+        stream = torch.cuda.current_stream()
+    return stream.cuda_stream
 
 
 def _check(rc, where):
