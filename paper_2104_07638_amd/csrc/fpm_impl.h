@@ -117,11 +117,14 @@ struct Opts {
     int* part;       // split > 1: per-item info codes, combined by the last deferred-correction launch
 };
 
-// Most work items per matrix of a uniform launch with deferred top-level corrections: each
-// of g items takes 2^T / g consecutive chunks, so that one matrix with many shifted pivots
-// (whose corrections reread its minors) spreads over several wavefronts instead of holding
-// one.
-constexpr int kSplit = 4;
+// Work items per matrix of a uniform launch with deferred top-level corrections: each of g
+// items takes 2^T / g consecutive chunks, so that one matrix with many shifted pivots (whose
+// corrections reread its minors) spreads over several wavefronts instead of holding one, and
+// a small batch fills the chip: up to kSplit items as the type gains from them (SplitOf), more
+// for small batches (the queue holds split_parts(batch) info codes).
+constexpr int kSplitItems = 8192;
+constexpr int kSplit = 8;
+constexpr int64_t split_parts(int64_t batch) { return batch * kSplit > kSplitItems ? batch * kSplit : kSplitItems; }
 
 // Deferred top-level corrections.  A wavefront whose matrix has shifted pivots in the top
 // levels records them in the matrix's slot of a queue instead of applying the corrections
@@ -130,7 +133,7 @@ constexpr int kSplit = 4;
 // [1] workgroups done; from int kTopHead on, one slot of kTopEntryInts per matrix: out (2),
 // ex (2), es_true (1), the shift code of each top node by chunk (8 ints = 32 bytes), the
 // listed flag (1); then the list (cap ints); then, for split launches, the info code of each
-// work item (cap * kSplit ints).  Ints 2 .. 2 + kTopCounts - 1 of the head are the completion
+// work item (split_parts(cap) ints).  Ints 2 .. 2 + kTopCounts - 1 of the head are the completion
 // counts of the correction launch.  Codes, flags and counts are zero between uses.
 constexpr int kTopDeferMaxT = 5;
 constexpr int kTopEntryInts = 14;
@@ -720,40 +723,20 @@ __device__ __forceinline__ int fpm_wave(const typename F::In* __restrict__ A, vo
 
     // ---- top-level corrections, deepest first ---------------------------------------
     if constexpr (T > 0) {
-        bool deferred = false;
-        if constexpr (T <= kTopDeferMaxT) {
-            if (any_top && o.topq && mat < o.topq_cap) {
-                // the matrix's slot: every item of a split matrix writes the same header and
-                // the codes of its own chunks; the first to set the flag lists the matrix
-                deferred = true;
-                int* ent = o.topq + kTopHead + (int64_t)mat * kTopEntryInts;
-                if (lane == 0) {
-                    const uint64_t po = reinterpret_cast<uint64_t>(out), pe = reinterpret_cast<uint64_t>(ex);
-                    ent[0] = (int)(uint32_t)po;
-                    ent[1] = (int)(uint32_t)(po >> 32);
-                    ent[2] = (int)(uint32_t)pe;
-                    ent[3] = (int)(uint32_t)(pe >> 32);
-                    ent[4] = pc.es_true;
-                }
-                int8_t* tv = reinterpret_cast<int8_t*>(ent + kTopCodes);
-                for (int c = c0 + lane; c < c1; c += kWave) tv[c] = tevc[c];
-                if (lane == 0) {
-                    const bool first = nsplit == 1 || atomicExch(ent + kTopFlag, 1) == 0;
-                    if (first) {
-                        int* list = o.topq + kTopHead + (int64_t)o.topq_cap * kTopEntryInts;
-                        list[atomicAdd(o.topq, 1)] = mat;
-                    }
-                }
-            }
-        }
-        if (any_top && !deferred && nsplit > 1) return -3;   // cannot happen: the queue holds every item
-        if (any_top && !deferred) {
+        // up to kTopDeferMaxT levels: all of them are left to the follow-up launch.  More: the item
+        // corrects the levels inside its own chunks here, and leaves those above (whose nodes
+        // span several items; its first chunk's code) to that launch.
+        constexpr bool kAll = T <= kTopDeferMaxT;
+        const int above = __builtin_ctz((unsigned)nsplit);     // levels above the item
+        const bool queue = o.topq && mat < o.topq_cap;
+        if (nsplit > 1 && !queue && any_top) return -3;         // cannot happen: the queue holds every item
+        if (any_top && !(kAll && queue)) {
             wave_mem_fence();
-            for (int d = T - 1; d >= 0; --d) {
+            for (int d = T - 1; d >= above; --d) {
                 const int step = 1 << (T - 1 - d);
                 const int64_t half = int64_t(1) << (N - 1 - d);
                 bool did = false;
-                for (int c = step; c < (1 << T); c += 2 * step) {
+                for (int c = c0 + step; c < c1; c += 2 * step) {
                     const int de = tevc[c];
                     if (de == kNoEv) continue;
                     did = true;
@@ -778,6 +761,33 @@ __device__ __forceinline__ int fpm_wave(const typename F::In* __restrict__ A, vo
                     }
                 }
                 if (did) wave_mem_fence();
+            }
+        }
+        const bool mine = kAll ? any_top : nsplit > 1 && c0 > 0 && tevc[c0] != kNoEv;
+        if (queue && mine) {
+            // the matrix's slot: every item of a split matrix writes the same header and the codes
+            // of its own chunks (of itself); the first to set the flag lists the matrix
+            int* ent = o.topq + kTopHead + (int64_t)mat * kTopEntryInts;
+            if (lane == 0) {
+                const uint64_t po = reinterpret_cast<uint64_t>(out), pe = reinterpret_cast<uint64_t>(ex);
+                ent[0] = (int)(uint32_t)po;
+                ent[1] = (int)(uint32_t)(po >> 32);
+                ent[2] = (int)(uint32_t)pe;
+                ent[3] = (int)(uint32_t)(pe >> 32);
+                ent[4] = pc.es_true;
+            }
+            int8_t* tv = reinterpret_cast<int8_t*>(ent + kTopCodes);
+            if constexpr (kAll) {
+                for (int c = c0 + lane; c < c1; c += kWave) tv[c] = tevc[c];
+            } else {
+                if (lane == 0) tv[g] = tevc[c0];
+            }
+            if (lane == 0) {
+                const bool first = nsplit == 1 || atomicExch(ent + kTopFlag, 1) == 0;
+                if (first) {
+                    int* list = o.topq + kTopHead + (int64_t)o.topq_cap * kTopEntryInts;
+                    list[atomicAdd(o.topq, 1)] = mat;
+                }
             }
         }
     }
@@ -824,17 +834,17 @@ __global__ __launch_bounds__(64) APM_FPM_OCC void fpm_uniform_kernel(const typen
 // the slots that were used and resets the queue's counters.
 constexpr int kTopFixThreads = 512;   // two work items in flight per workgroup (256 threads each)
 
-template <class F, int N, int K0MAX>
+// T levels: all top levels of a matrix of order N, or those above the items of a split one.
+template <class F, int N, int T>
 __global__ __launch_bounds__(kTopFixThreads) void fpm_topfix_kernel(int* topq, int cap, int f64, const int* part,
                                                                     int split, int32_t* info, int batch)
 {
-    using P = Plan<N, K0MAX>;
-    constexpr int T = P::T, K = P::K;
+    constexpr int K = N - T;
     constexpr int kSub = kTopFixThreads / 256;
     const int tid = threadIdx.x;
     __shared__ int last_s;
     int count = 0;
-    if constexpr (T > 0 && T <= kTopDeferMaxT) {
+    {
         constexpr int NC = 1 << T;
         constexpr int kTiles = (1 << K) / 256;
         static_assert(kTiles >= 1 && (1 << K) % 256 == 0, "chunks hold whole tiles");
@@ -916,7 +926,7 @@ __global__ __launch_bounds__(kTopFixThreads) void fpm_topfix_kernel(int* topq, i
     }
     __syncthreads();
     if (last_s) {
-        if constexpr (T > 0 && T <= kTopDeferMaxT) {
+        {
             // clear the codes and flags of the listed slots (the next launch fills them anew)
             const int* list = topq + kTopHead + (int64_t)cap * kTopEntryInts;
             constexpr int kClr = kTopEntryInts - kTopCodes;
@@ -966,6 +976,23 @@ static_assert(SplitOf<FR64>::v <= kSplit && SplitOf<FR32S>::v <= kSplit && Split
 // a batch that is shifted throughout in flight.
 constexpr int kTopFixGroups = 256;
 
+template <class F, int N, int T>
+hipError_t launch_topfix(int* topq, const Opts& o, const LaunchMinors& L, hipStream_t st)
+{
+    hipLaunchKernelGGL((fpm_topfix_kernel<F, N, T>), dim3(kTopFixGroups), dim3(kTopFixThreads), 0, st, topq, o.topq_cap,
+                       L.out_f64 ? 1 : 0, o.part, o.split, L.info, L.batch);
+    return hipGetLastError();
+}
+
+template <class F, int N, int T>
+hipError_t launch_topfix_from(int levels, int* topq, const Opts& o, const LaunchMinors& L, hipStream_t st)
+{
+    if constexpr (T < kTopDeferMaxT) {
+        if (levels > T) return launch_topfix_from<F, N, T + 1>(levels, topq, o, L, st);
+    }
+    return launch_topfix<F, N, T>(topq, o, L, st);
+}
+
 template <class F, int N, int K0>
 hipError_t launch_uniform(const LaunchMinors& L, hipStream_t st)
 {
@@ -977,24 +1004,48 @@ hipError_t launch_uniform(const LaunchMinors& L, hipStream_t st)
         if (e != hipSuccess) return e;
     }
     constexpr int T = Plan<N, K0>::T;
-    constexpr bool kDefer = T > 0 && T <= kTopDeferMaxT;
-    int* topq = kDefer ? L.topq : nullptr;
-    // split matrices into work items (the queue holds a slot per matrix and an info code
-    // per item of kSplit): with one wavefront per matrix, a few matrices with many shifted
-    // pivots (whose corrections reread their minors) or a batch of few matrices set the end
-    // of the launch.  Items per matrix by type, measured on MI355X: fp64 2 (stressed 8192 x
-    // 16 batch 1.00 -> 0.97 ms; unstressed 0.92 -> 0.935), fp32-scaled 4 (stressed batch
-    // 1.46 -> 1.10 ms), complex128 2 (4096 x 14 Keldysh 0.602 -> 0.582 ms), complex64-scaled
-    // 1 (the same batch 0.304 ms; 2 items 0.309, 4 items 0.327).
-    const int split = (topq && !L.no_split) ? (SplitOf<F>::v < (1 << T) ? SplitOf<F>::v : (1 << T)) : 1;
+    int* topq = T > 0 ? L.topq : nullptr;
+    // split matrices into work items (the queue holds a slot per matrix and an info code per
+    // item): with one wavefront per matrix, a few matrices with many shifted pivots (whose
+    // corrections reread their minors) or a batch of few matrices set the end of the launch.
+    // Items per matrix by type, measured on MI355X: fp64 2 (stressed 8192 x 16 batch 1.00 ->
+    // 0.97 ms; unstressed 0.92 -> 0.935), fp32-scaled 4 (stressed batch 1.46 -> 1.10 ms),
+    // complex128 2 (4096 x 14 Keldysh 0.602 -> 0.582 ms), complex64-scaled 1 (the same batch
+    // 0.304 ms; 2 items 0.309, 4 items 0.327).
+    // Small batches take more, up to 2^kTopDeferMaxT, while the wavefronts that fit the chip at
+    // once hold them (64 fp64 matrices of order 16 102 -> 25 us; past that the items only repeat
+    // the levels above them: 500 complex128 of order 14 96 us with 2 each, 109 with 4).  Orders
+    // with more top levels (17 and up in fp64, 15 and up complex) have long items: they take
+    // more until the last round of wavefronts leaves less than 15% of all idle (order 18, 1000
+    // in fp64 1.10 -> 0.55 ms, 20 complex128 2.29 -> 0.10 ms; 1024 complex128 of order 16, which fit
+    // exactly, 0.64 ms with 1 each, 0.79 with 2, 0.77 with 4).
+    constexpr int kMost = T < kTopDeferMaxT ? T : kTopDeferMaxT;
+    constexpr int64_t kFit = 256 * (Ly::bytes * 8 <= 163840 ? 8 : 163840 / Ly::bytes);
+    static_assert(kFit <= kSplitItems, "the queue holds the info codes");
+    int levels = 0;
+    if (topq && !L.no_split) {
+        const int64_t B = L.batch;
+        while (levels < kMost && (1 << levels) < SplitOf<F>::v && !(F::kComplex && T > kTopDeferMaxT)) ++levels;
+        if constexpr (T > kTopDeferMaxT) {
+            auto idle = [&](int64_t items) { return (items + kFit - 1) / kFit * kFit * 85 > items * 100; };
+            while (levels < kMost && idle(B << levels) && (B << (levels + 1)) <= split_parts(B)) ++levels;
+        } else {
+            while (levels < kMost && (B << (levels + 1)) <= kFit) ++levels;
+        }
+    }
+    const int split = 1 << levels;
     int* part = topq ? topq + kTopHead + (int64_t)L.topq_cap * (kTopEntryInts + 1) : nullptr;
     Opts o{L.tau, L.perturb, L.out_f64, topq, topq ? L.topq_cap : 0, split, part};
     hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)L.batch * split)), dim3(64), Ly::bytes, st,
                        static_cast<const typename F::In*>(L.A), L.out, L.ex, L.info, L.batch, L.in_off, L.out_off, o);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !topq) return e;
-    hipLaunchKernelGGL((fpm_topfix_kernel<F, N, K0>), dim3(kTopFixGroups), dim3(kTopFixThreads), 0, st, topq, o.topq_cap,
-                       L.out_f64 ? 1 : 0, part, split, L.info, L.batch);
+    if constexpr (T > kTopDeferMaxT) {
+        if (levels == 0) return hipSuccess;      // one item per matrix has corrected all levels itself
+        return launch_topfix_from<F, N, 1>(levels, topq, o, L, st);
+    } else if constexpr (T > 0) {
+        return launch_topfix<F, N, T>(topq, o, L, st);
+    }
     return hipGetLastError();
 }
 
