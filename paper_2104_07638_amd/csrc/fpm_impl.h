@@ -57,19 +57,24 @@ struct Plan {
 constexpr int sq(int x) { return x * x; }
 constexpr int nz(int x) { return x > 0 ? x : 1; }
 
-// Per-wave LDS layout: matrices (units of E), then small typed arrays.
-template <class F, int N, int K0MAX>
+// Per-wave LDS layout: matrices (units of E), then small typed arrays.  Q: the matrices of the
+// first Q top levels are needed only for the path to the item's first chunk (a matrix split into
+// 2^Q items or more) and share the breadth-first buffers, which come into use after it.
+template <class F, int N, int K0MAX, int Q = 0>
 struct Lay {
     using P = Plan<N, K0MAX>;
     using E = typename F::E;
     using R = typename F::R;
     using Bs = typename F::Bs;
-    static constexpr int top_off(int d)
+    static constexpr int kPath = Q;
+    static constexpr int sum_sq(int a, int b)
     {
         int s = 0;
-        for (int i = 0; i < d; ++i) s += sq(N - i);
+        for (int i = a; i < b; ++i) s += sq(N - i);
         return s;
     }
+    static constexpr int nTop = sum_sq(Q, P::T + 1);          // the matrices that stay
+    static constexpr int top_off(int d) { return d < Q ? nTop + sum_sq(0, d) : sum_sq(Q, d); }
     // Mid levels 0..bf-1 are expanded breadth-first into compact matrices: BF level j
     // (1..bf) holds all 2^j nodes of order K-j; odd and even levels alternate buffers.
     // Rows are padded to an odd number of elements, so that lanes reading the same column
@@ -89,7 +94,8 @@ struct Lay {
         for (int j = 2; j <= P::bf; j += 2) m = lvl(j) > m ? lvl(j) : m;
         return m;
     }
-    static constexpr int nE = top_off(P::T + 1) + bufA() + bufB();
+    static constexpr int nBuf = bufA() + bufB() > sum_sq(0, Q) ? bufA() + bufB() : sum_sq(0, Q);
+    static constexpr int nE = nTop + nBuf;
     static constexpr int nPiv = nz((1 << P::bf) - 1);   // mid nodes expanded breadth-first
     static constexpr size_t al(size_t x) { return (x + 15) & ~size_t(15); }
     static constexpr size_t oE = 0;
@@ -104,7 +110,7 @@ struct Lay {
     static constexpr size_t oMid = al(oTev + (size_t(1) << P::T));        // int8 [2][64]: two chunks
     static constexpr size_t bytes = al(oMid + 128);
     // element offset of BF level j (j >= 1); node q of that level starts at q ns(K-j)
-    static constexpr int lvl_base(int j) { return top_off(P::T + 1) + ((j & 1) ? 0 : bufA()); }
+    static constexpr int lvl_base(int j) { return nTop + ((j & 1) ? 0 : bufA()); }
 };
 
 struct Opts {
@@ -310,13 +316,13 @@ constexpr int bf_cols(int rows, int m)
 // (t, a) writes row a of both children of node (J, t) -- the left child (the trailing
 // block) and the right child (the Schur complement), or a group of its columns.  Every
 // lane of a node repeats the node's pivot analysis; one lane publishes it.
-template <class F, int N, int K0MAX, int J>
+template <class F, int N, int K0MAX, int Q, int J>
 __device__ __forceinline__ void bf_levels(typename F::E* lds, typename F::E* pt_a, typename F::E* pu_a,
                                           typename F::R* ri_a, int8_t* midc, int x0o, int x0l, int lane,
                                           const PivCtl& pc, bool& mid_any)
 {
     using P = Plan<N, K0MAX>;
-    using L = Lay<F, N, K0MAX>;
+    using L = Lay<F, N, K0MAX, Q>;
     using E = typename F::E;
     if constexpr (J < P::bf) {
         constexpr int nodes = 1 << J;
@@ -368,17 +374,17 @@ __device__ __forceinline__ void bf_levels(typename F::E* lds, typename F::E* pt_
         }
         mid_any |= ballot(pert) != 0;
         wave_sync();
-        bf_levels<F, N, K0MAX, J + 1>(lds, pt_a, pu_a, ri_a, midc, x0o, x0l, lane, pc, mid_any);
+        bf_levels<F, N, K0MAX, Q, J + 1>(lds, pt_a, pu_a, ri_a, midc, x0o, x0l, lane, pc, mid_any);
     }
 }
 
 // Top level D: take the right branch of the depth-D node (Schur complement of order
 // N-D-1 into top storage D+1), a column per lane over groups of rows.  Returns the pivot
 // analysis.
-template <class F, int N, int K0MAX, int D>
+template <class F, int N, int K0MAX, int Q, int D>
 __device__ __forceinline__ PivInfo<F> top_right(typename F::E* lds, int xo, int xl, int lane, const PivCtl& pc)
 {
-    using L = Lay<F, N, K0MAX>;
+    using L = Lay<F, N, K0MAX, Q>;
     using E = typename F::E;
     constexpr int m = N - D - 1;
     const E* X = lds + xo;
@@ -403,14 +409,14 @@ __device__ __forceinline__ PivInfo<F> top_right(typename F::E* lds, int xo, int 
     return pv;
 }
 
-template <class F, int N, int K0MAX, int D>
+template <class F, int N, int K0MAX, int Q, int D>
 __device__ __forceinline__ PivInfo<F> top_right_at(int d, typename F::E* lds, int xo, int xl, int lane,
                                                    const PivCtl& pc)
 {
     if constexpr (D + 1 < Plan<N, K0MAX>::T) {
-        if (d != D) return top_right_at<F, N, K0MAX, D + 1>(d, lds, xo, xl, lane, pc);
+        if (d != D) return top_right_at<F, N, K0MAX, Q, D + 1>(d, lds, xo, xl, lane, pc);
     }
-    return top_right<F, N, K0MAX, D>(lds, xo, xl, lane, pc);
+    return top_right<F, N, K0MAX, Q, D>(lds, xo, xl, lane, pc);
 }
 
 // Cross-lane exchange of a correction value (fp64, or the two halves of a complex value).
@@ -507,12 +513,12 @@ __device__ __forceinline__ void fix_chunk(void* out, int16_t* ex, int c, int lan
 }
 
 // All principal minors of one N x N matrix by one wavefront.  Returns the info code.
-template <class F, int N, int K0MAX>
+template <class F, int N, int K0MAX, int Q = 0>
 __device__ __forceinline__ int fpm_wave(const typename F::In* __restrict__ A, void* out, int16_t* ex,
                                         unsigned char* lds_raw, const Opts& o, int g = 0, int mat = 0)
 {
     using P = Plan<N, K0MAX>;
-    using L = Lay<F, N, K0MAX>;
+    using L = Lay<F, N, K0MAX, Q>;
     using E = typename F::E;
     using R = typename F::R;
     using Bs = typename F::Bs;
@@ -559,11 +565,11 @@ __device__ __forceinline__ int fpm_wave(const typename F::In* __restrict__ A, vo
         const int a = i / N, b = i - (i / N) * N;
         const int pa = a < T ? N - 1 - a : a - T;
         const int pb = b < T ? N - 1 - b : b - T;
-        lds[i] = F::conv(A[pa * N + pb], sc);
+        lds[L::top_off(0) + i] = F::conv(A[pa * N + pb], sc);
     }
     for (int c = lane; c < (1 << T); c += kWave) tevc[c] = kNoEv;
     if (lane <= T) {
-        off_a[lane] = lane * (N + 1);
+        off_a[lane] = L::top_off(0) + lane * (N + 1);
         ld_a[lane] = N;
         bu_a[lane] = F::one();
         rec_a[lane] = F::one();
@@ -586,7 +592,7 @@ __device__ __forceinline__ int fpm_wave(const typename F::In* __restrict__ A, vo
     auto top_step = [&](int d, int c, bool own) {
       if constexpr (T > 0) {
         const int m = N - d - 1;
-        const PivInfo<F> pv = top_right_at<F, N, K0MAX, 0>(d, lds, off_a[d], ld_a[d], lane, pc);
+        const PivInfo<F> pv = top_right_at<F, N, K0MAX, Q, 0>(d, lds, off_a[d], ld_a[d], lane, pc);
         const Bs bud = bu_a[d];
         if (pv.pert && own) {
             nev += 1;
@@ -604,10 +610,30 @@ __device__ __forceinline__ int fpm_wave(const typename F::In* __restrict__ A, vo
         wave_sync();
       }
     };
+    // After level Q - 1 of the path: its matrix of order N - Q into the storage that stays.
+    auto keep_path = [&]() {
+        constexpr int m = N - Q;
+        const int xo = off_a[Q], xl = ld_a[Q];
+        if (xo == L::top_off(Q)) return;
+        for (int i = lane; i < m * m; i += kWave) {
+            const int a = i / m, b = i - a * m;
+            lds[L::top_off(Q) + i] = lds[xo + a * xl + b];
+        }
+        wave_sync();
+        for (int dd = Q + lane; dd <= T; dd += kWave) {
+            off_a[dd] = L::top_off(Q) + (dd - Q) * (m + 1);
+            ld_a[dd] = m;
+        }
+        wave_sync();
+    };
     if constexpr (T > 0) {
         // the path to the item's first chunk: a right branch for every set bit of c0
-        for (int d = 0; d < T; ++d)
+        for (int d = 0; d < T; ++d) {
+            if constexpr (Q > 0) {
+                if (d == Q) keep_path();
+            }
             if ((c0 >> (T - 1 - d)) & 1) top_step(d, c0, d == T - 1 - __builtin_ctz((unsigned)c0));
+        }
     }
 
     for (int c = c0; c < c1; ++c) {
@@ -619,7 +645,7 @@ __device__ __forceinline__ int fpm_wave(const typename F::In* __restrict__ A, vo
 
         // ---- mid levels 0..bf-1: breadth-first in LDS --------------------------------
         bool mid_any = false;
-        bf_levels<F, N, K0MAX, 0>(lds, pt_a, pu_a, ri_a, midc, x0o, x0l, lane, pc, mid_any);
+        bf_levels<F, N, K0MAX, Q, 0>(lds, pt_a, pu_a, ri_a, midc, x0o, x0l, lane, pc, mid_any);
 
         // ---- the previous chunk's pivot corrections -----------------------------------
         if (pend) fix_chunk<F, N, K0MAX>(out, ex, c - 1, lane, o.out_f64, pev, plc0, plc1,
@@ -796,7 +822,7 @@ __device__ __forceinline__ int fpm_wave(const typename F::In* __restrict__ A, vo
 }
 
 // ------------------------------------------------------------------------------ kernels
-template <class F, int N, int K0MAX>
+template <class F, int N, int K0MAX, int Q>
 __global__ __launch_bounds__(64) APM_FPM_OCC void fpm_uniform_kernel(const typename F::In* __restrict__ A, void* out,
                                                          int16_t* ex, int32_t* info, int32_t batch,
                                                          const int64_t* __restrict__ in_off,
@@ -816,7 +842,7 @@ __global__ __launch_bounds__(64) APM_FPM_OCC void fpm_uniform_kernel(const typen
                                         : (void*)(static_cast<float*>(out) + oo);
     }
     int16_t* eb = ex ? ex + oo : nullptr;
-    const int r = fpm_wave<F, N, K0MAX>(A + io, ob, eb, lds_dyn, o, g, b);
+    const int r = fpm_wave<F, N, K0MAX, Q>(A + io, ob, eb, lds_dyn, o, g, b);
     if (lane_id() == 0) {
         if (G > 1) o.part[blockIdx.x] = r;
         else if (info) info[b] = r;
@@ -962,6 +988,22 @@ inline int env_k0()
     return e ? atoi(e) : 0;
 }
 
+// Wavefronts of a kernel that a CU holds: by LDS, and two per SIMD by registers.
+constexpr int waves_per_cu(size_t bytes) { return bytes * 8 <= 163840 ? 8 : (int)(163840 / bytes); }
+
+// Top levels whose matrices share the breadth-first buffers in split launches: two for complex128
+// where that makes room for more wavefronts (order 14: 8 instead of 6 per CU, 4096 matrices in
+// 4 items each 546 -> 453 us; order 15 727 -> 501).  The other types hold eight without.
+template <class F, int N, int K0>
+constexpr int path_levels()
+{
+    if constexpr (F::kId == FC128::kId && Plan<N, K0>::T > 2) {
+        return waves_per_cu(Lay<F, N, K0>::bytes) < waves_per_cu(Lay<F, N, K0, 2>::bytes) ? 2 : 0;
+    } else {
+        return 0;
+    }
+}
+
 template <class F> struct SplitOf;
 template <> struct SplitOf<FR64> { static constexpr int v = 2; };
 template <> struct SplitOf<FR32S> { static constexpr int v = 4; };
@@ -996,21 +1038,17 @@ hipError_t launch_topfix_from(int levels, int* topq, const Opts& o, const Launch
 template <class F, int N, int K0>
 hipError_t launch_uniform(const LaunchMinors& L, hipStream_t st)
 {
-    using Ly = Lay<F, N, K0>;
-    auto kern = fpm_uniform_kernel<F, N, K0>;
-    if (Ly::bytes > 65536) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)Ly::bytes);
-        if (e != hipSuccess) return e;
-    }
     constexpr int T = Plan<N, K0>::T;
+    constexpr int Q = path_levels<F, N, K0>();
+    constexpr int kItems = Q > 0 ? 1 << Q : SplitOf<F>::v;
+    using Ly = Lay<F, N, K0, Q>;
     int* topq = T > 0 ? L.topq : nullptr;
     // split matrices into work items (the queue holds a slot per matrix and an info code per
     // item): with one wavefront per matrix, a few matrices with many shifted pivots (whose
     // corrections reread their minors) or a batch of few matrices set the end of the launch.
     // Items per matrix by type, measured on MI355X: fp64 2 (stressed 8192 x 16 batch 1.00 ->
     // 0.97 ms; unstressed 0.92 -> 0.935), fp32-scaled 4 (stressed batch 1.46 -> 1.10 ms),
-    // complex128 2 (4096 x 14 Keldysh 0.602 -> 0.582 ms), complex64-scaled 1 (the same batch
+    // complex128 2 (4096 x 14 Keldysh 0.602 -> 0.582 ms; 4 where path_levels shares LDS), complex64-scaled 1 (the same batch
     // 0.304 ms; 2 items 0.309, 4 items 0.327).
     // Small batches take more, up to 2^kTopDeferMaxT, while the wavefronts that fit the chip at
     // once hold them (64 fp64 matrices of order 16 102 -> 25 us; past that the items only repeat
@@ -1020,12 +1058,12 @@ hipError_t launch_uniform(const LaunchMinors& L, hipStream_t st)
     // in fp64 1.10 -> 0.55 ms, 20 complex128 2.29 -> 0.10 ms; 1024 complex128 of order 16, which fit
     // exactly, 0.64 ms with 1 each, 0.79 with 2, 0.77 with 4).
     constexpr int kMost = T < kTopDeferMaxT ? T : kTopDeferMaxT;
-    constexpr int64_t kFit = 256 * (Ly::bytes * 8 <= 163840 ? 8 : 163840 / Ly::bytes);
+    constexpr int64_t kFit = 256 * waves_per_cu(Ly::bytes);
     static_assert(kFit <= kSplitItems, "the queue holds the info codes");
     int levels = 0;
     if (topq && !L.no_split) {
         const int64_t B = L.batch;
-        while (levels < kMost && (1 << levels) < SplitOf<F>::v && !(F::kComplex && T > kTopDeferMaxT)) ++levels;
+        while (levels < kMost && (1 << levels) < kItems && !(F::kComplex && T > kTopDeferMaxT)) ++levels;
         if constexpr (T > kTopDeferMaxT) {
             auto idle = [&](int64_t items) { return (items + kFit - 1) / kFit * kFit * 85 > items * 100; };
             while (levels < kMost && idle(B << levels) && (B << (levels + 1)) <= split_parts(B)) ++levels;
@@ -1036,7 +1074,15 @@ hipError_t launch_uniform(const LaunchMinors& L, hipStream_t st)
     const int split = 1 << levels;
     int* part = topq ? topq + kTopHead + (int64_t)L.topq_cap * (kTopEntryInts + 1) : nullptr;
     Opts o{L.tau, L.perturb, L.out_f64, topq, topq ? L.topq_cap : 0, split, part};
-    hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)L.batch * split)), dim3(64), Ly::bytes, st,
+    // (fewer items than 2^Q: the layout that holds all top levels)
+    const bool path = Q > 0 && levels >= Q;
+    const size_t bytes = path ? Ly::bytes : Lay<F, N, K0>::bytes;
+    auto kern = path ? fpm_uniform_kernel<F, N, K0, Q> : fpm_uniform_kernel<F, N, K0, 0>;
+    if (bytes > 65536) {
+        const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)L.batch * split)), dim3(64), bytes, st,
                        static_cast<const typename F::In*>(L.A), L.out, L.ex, L.info, L.batch, L.in_off, L.out_off, o);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !topq) return e;
