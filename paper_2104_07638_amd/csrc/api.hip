@@ -482,13 +482,13 @@ struct apm_plan {
     hipStream_t ps = nullptr;     // private stream the graph is recorded on
     hipGraph_t g = nullptr;
     hipGraphExec_t ge = nullptr;
-    bool few = false;             // few kernels: launched one by one outside capture
+    bool few = false;             // few kernels: launched one by one
 };
 
 namespace {
 
-// Plans of up to this many kernels enqueue them one by one (3.3 us of host time each) and use
-// their graph only when the stream is being captured: a graph launch takes 20 us of host time and
+// Plans of up to this many kernels enqueue them one by one (3.3 us of host time each; under
+// capture they become nodes of the caller's graph): a graph launch takes 20 us of host time and
 // the kernels of a graph start further apart.  One kernel: 20.6 -> 5.1 us a launch; the CDet plan of
 // 200 matrices of 5 to 7 vertices (3 kernels) 33 -> 17.5 us, of 100 of 6 to 11 (5) 51 -> 46, two
 // spins (7) 63 -> 59.  The widest mixed plans (10 kernels) stay graphs.
@@ -1121,20 +1121,18 @@ apm_status apm_plan_launch(apm_plan* p, apm_stream stream)
     if (e != hipSuccess) return from_hip(e);
     if (dev != p->dev) return APM_EINVAL;
     const hipStream_t st = (hipStream_t)stream;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (p->few || p->dirty) {
+    if (p->ge && !p->few) return from_hip(hipGraphLaunch(p->ge, st));
+    if (p->dirty) {
+        // a failed launch may have left deferred corrections queued: clear them (outside capture
+        // only; a plan is not recorded while in this state)
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         e = hipStreamIsCapturing(st, &cs);
         if (e != hipSuccess) return from_hip(e);
-    }
-    if (p->dirty) {
-        // a failed direct launch may have left deferred corrections queued: clear them
-        // (outside capture only; a plan is not recorded while in this state)
         if (cs != hipStreamCaptureStatusNone) return APM_EINVAL;
         e = hipMemsetAsync(p->ws, 0, p->ws_bytes, st);
         if (e != hipSuccess) return from_hip(e);
         p->dirty = false;
     }
-    if (p->ge && !(p->few && cs == hipStreamCaptureStatusNone)) return from_hip(hipGraphLaunch(p->ge, st));
     e = plan_enqueue(p, st);
     if (e != hipSuccess) p->dirty = true;
     return from_hip(e);
