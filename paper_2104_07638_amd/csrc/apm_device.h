@@ -200,6 +200,7 @@ struct FR64 {
     {
         static_cast<double*>(out)[i] = v;
     }
+    __device__ static V stored(V v, bool) { return v; }                 // as load_v gives back what store_v wrote
     __device__ static V sub_scaled(V a, double C, V b) { return fma(-C, b, a); }
     __device__ static void store_nan(void* out, int16_t*, int64_t i, bool)
     {
@@ -281,6 +282,13 @@ struct FR32S {
             ex[i] = (int16_t)(mf == 0.0f ? 0 : ee);
         }
     }
+    __device__ static V stored(V v, bool f64)                           // as load_v gives back what store_v wrote
+    {
+        if (f64) return v;
+        int e;
+        const double m = frexp(v, &e);
+        return ldexp((double)(float)m, e);
+    }
     __device__ static V sub_scaled(V a, double C, V b) { return fma(-C, b, a); }
     __device__ static void store_nan(void* out, int16_t* ex, int64_t i, bool f64)
     {
@@ -350,6 +358,7 @@ struct FC128 {
     {
         static_cast<cd*>(out)[i] = v;
     }
+    __device__ static V stored(V v, bool) { return v; }                 // as load_v gives back what store_v wrote
     __device__ static V sub_scaled(V a, double C, V b) { return {fma(-C, b.x, a.x), fma(-C, b.y, a.y)}; }
     __device__ static void store_nan(void* out, int16_t*, int64_t i, bool)
     {
@@ -453,6 +462,14 @@ struct FC64S {
             static_cast<cf*>(out)[i] = m;
             ex[i] = (int16_t)ee;
         }
+    }
+    __device__ static V stored(V v, bool f64)                           // as load_v gives back what store_v wrote
+    {
+        if (f64) return v;
+        const double big = fmax(fabs(v.x), fabs(v.y));
+        int e = 0;
+        if (big != 0.0) (void)frexp(big, &e);
+        return {ldexp((double)(float)ldexp(v.x, -e), e), ldexp((double)(float)ldexp(v.y, -e), e)};
     }
     __device__ static V sub_scaled(V a, double C, V b) { return {fma(-C, b.x, a.x), fma(-C, b.y, a.y)}; }
     __device__ static void store_nan(void* out, int16_t* ex, int64_t i, bool f64)

@@ -860,8 +860,10 @@ __global__ __launch_bounds__(64) APM_FPM_OCC void fpm_uniform_kernel(const typen
 // the slots that were used and resets the queue's counters.
 constexpr int kTopFixThreads = 512;   // two work items in flight per workgroup (256 threads each)
 
-// T levels: all top levels of a matrix of order N, or those above the items of a split one.
-template <class F, int N, int T>
+// T levels: all top levels of a matrix of order N, or (kAbove) those above the items of a split
+// one, whose values are rounded to the output type between levels, as the items themselves
+// and a matrix in one item do by storing them.
+template <class F, int N, int T, bool kAbove>
 __global__ __launch_bounds__(kTopFixThreads) void fpm_topfix_kernel(int* topq, int cap, int f64, const int* part,
                                                                     int split, int32_t* info, int batch)
 {
@@ -894,7 +896,8 @@ __global__ __launch_bounds__(kTopFixThreads) void fpm_topfix_kernel(int* topq, i
             for (int c = 1; c < NC; ++c) {
                 if (code(c) != kNoEv) {
                     const int st = c & -c;
-                    wm |= ((1u << st) - 1) << c;
+                    // (above: what no level changes is not stored again, a zero keeps its exponent)
+                    wm |= (((1u << st) - 1) & (kAbove && j == 0 ? ~1u : ~0u)) << c;
                     rm |= ((1u << st) - 1) << (c - st);
                 }
             }
@@ -914,7 +917,10 @@ __global__ __launch_bounds__(kTopFixThreads) void fpm_topfix_kernel(int* topq, i
                     const double Ct = shift_value(es, de);
 #pragma unroll
                     for (int u = 0; u < st; ++u)
-                        if (u != 0 || j != 0) x[c + u] = F::sub_scaled(x[c + u], Ct, x[c + u - st]);
+                        if (u != 0 || j != 0) {
+                            x[c + u] = F::sub_scaled(x[c + u], Ct, x[c + u - st]);
+                            if constexpr (kAbove) x[c + u] = F::stored(x[c + u], f64 != 0);
+                        }
                 }
             }
 #pragma unroll
@@ -1018,10 +1024,10 @@ static_assert(SplitOf<FR64>::v <= kSplit && SplitOf<FR32S>::v <= kSplit && Split
 // a batch that is shifted throughout in flight.
 constexpr int kTopFixGroups = 256;
 
-template <class F, int N, int T>
+template <class F, int N, int T, bool kAbove>
 hipError_t launch_topfix(int* topq, const Opts& o, const LaunchMinors& L, hipStream_t st)
 {
-    hipLaunchKernelGGL((fpm_topfix_kernel<F, N, T>), dim3(kTopFixGroups), dim3(kTopFixThreads), 0, st, topq, o.topq_cap,
+    hipLaunchKernelGGL((fpm_topfix_kernel<F, N, T, kAbove>), dim3(kTopFixGroups), dim3(kTopFixThreads), 0, st, topq, o.topq_cap,
                        L.out_f64 ? 1 : 0, o.part, o.split, L.info, L.batch);
     return hipGetLastError();
 }
@@ -1032,7 +1038,7 @@ hipError_t launch_topfix_from(int levels, int* topq, const Opts& o, const Launch
     if constexpr (T < kTopDeferMaxT) {
         if (levels > T) return launch_topfix_from<F, N, T + 1>(levels, topq, o, L, st);
     }
-    return launch_topfix<F, N, T>(topq, o, L, st);
+    return launch_topfix<F, N, T, true>(topq, o, L, st);
 }
 
 template <class F, int N, int K0>
@@ -1090,7 +1096,7 @@ hipError_t launch_uniform(const LaunchMinors& L, hipStream_t st)
         if (levels == 0) return hipSuccess;      // one item per matrix has corrected all levels itself
         return launch_topfix_from<F, N, 1>(levels, topq, o, L, st);
     } else if constexpr (T > 0) {
-        return launch_topfix<F, N, T>(topq, o, L, st);
+        return launch_topfix<F, N, T, false>(topq, o, L, st);
     }
     return hipGetLastError();
 }
