@@ -29,7 +29,7 @@
  *     whose stream has no queue of the batch's size applies those corrections inside
  *     the minors kernel (same results, bit for bit).  A graph that did capture a queue
  *     uses the capturing stream's buffer: its replays must not overlap direct calls on
- *     that stream.  Like the workspace, a queue (and the XOR minors' per-stream node
+ *     that stream.  Like the workspace, a queue (and the NAND minors' per-stream
  *     workspace) is never freed when a larger one replaces it.
  *   - Calls are asynchronous: arguments are validated on the host, work is
  *     enqueued on `stream`, and the call returns.  Results are valid once the
@@ -209,10 +209,7 @@ apm_status apm_all_perm_minors(const double *A, const apm_batch *bd, double *per
  *           block i) are the last 2^n entries.
  *   info    [B] int32 or NULL: 0, -2 non-finite input (outputs NaN), or -3 a non-finite
  *           output (a zero pivot: this tree admits no pivot shift, Sec. III).
- * Matrices with more than six blocks use a workspace of the library per (device,
- * stream), 3 KB per matrix at n = 8 and 47 KB at n = 14 (complex128; half for double),
- * grown outside stream capture only (a captured call that would grow it returns
- * APM_EUNSUPPORTED).
+ * Needs no workspace: calls of any size can be captured.
  * Returns APM_OK, APM_EINVAL, APM_EUNSUPPORTED, APM_ENOMEM or APM_EDEVICE.
  */
 apm_status apm_xor_minors(apm_dtype dt, const void *A, const apm_batch *bd, void *out, int32_t *info,
@@ -228,7 +225,7 @@ apm_status apm_xor_minors(apm_dtype dt, const void *A, const apm_batch *bd, void
  *   dt, A, bd, info, stream   as for apm_xor_minors (info -3: a singular pivot block).
  *   out     [B x 2^n] output: entry mask is det A[R, R], R = the two rows of every block i
  *           with bit i of mask set; entry 0 = 1.
- * Uses the same per-(device, stream) workspace as apm_xor_minors.
+ * Needs no workspace.
  * Returns APM_OK, APM_EINVAL, APM_EUNSUPPORTED, APM_ENOMEM or APM_EDEVICE.
  */
 apm_status apm_xnor_minors(apm_dtype dt, const void *A, const apm_batch *bd, void *out, int32_t *info,
@@ -253,7 +250,10 @@ apm_status apm_xnor_minors(apm_dtype dt, const void *A, const apm_batch *bd, voi
  *   bd      uniform batch, n_uniform = n blocks, 1 <= n <= APM_MAX_N_NAND, no offsets.
  *   out     [B x 3^n]: entry sum_i t_i 3^i is the determinant over the kept rows, with
  *           t_i = 0 (block i left out), 1 (row 2i kept) or 2 (row 2i+1 kept); entry 0 = 1.
- * Uses the same per-(device, stream) workspace as apm_xor_minors.
+ * Matrices with more than six blocks use a workspace of the library per (device, stream):
+ * the top-level nodes of the matrices with pivot shifts, which a second launch computes, and
+ * a flag per matrix.  It is grown outside stream capture only (a captured call that would
+ * grow it returns APM_EUNSUPPORTED).
  * Returns APM_OK, APM_EINVAL, APM_EUNSUPPORTED, APM_ENOMEM or APM_EDEVICE.
  */
 apm_status apm_nand_minors(apm_dtype dt, const void *A, const apm_batch *bd, void *out, int32_t *info,
@@ -345,9 +345,10 @@ void apm_minors_k0_mixed(apm_dtype dt, int32_t *k0_small, int32_t *k0_large);
  * with APM_PLAN_AUTOTUNE, as apm_autotune_minors / apm_autotune_minors_mixed do, when
  * neither the process nor the tuning cache has a value for that dtype and order yet), and
  * records the whole launch sequence once into a HIP graph on a private stream.
- * apm_plan_launch then enqueues that graph on the caller's stream: one launch call for the
- * whole sequence, with results bit-identical to the direct calls.  With APM_PLAN_EAGER the
- * plan records nothing and each launch enqueues the kernels one by one (same results).
+ * apm_plan_launch then enqueues that graph on the caller's stream, or, for a plan of up to
+ * eight kernels, the kernels one by one (which costs less), with results bit-identical to the
+ * direct calls.  With APM_PLAN_EAGER the plan records nothing and each launch enqueues the
+ * kernels one by one (same results).
  *
  * The caller keeps every buffer named in the description (and the device arrays of its
  * apm_batch) alive and at the same addresses until apm_plan_destroy; their contents may
