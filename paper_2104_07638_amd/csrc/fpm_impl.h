@@ -1056,26 +1056,24 @@ hipError_t launch_uniform(const LaunchMinors& L, hipStream_t st)
     // 0.97 ms; unstressed 0.92 -> 0.935), fp32-scaled 4 (stressed batch 1.46 -> 1.10 ms),
     // complex128 2 (4096 x 14 Keldysh 0.602 -> 0.582 ms; 4 where path_levels shares LDS), complex64-scaled 1 (the same batch
     // 0.304 ms; 2 items 0.309, 4 items 0.327).
-    // Small batches take more, up to 2^kTopDeferMaxT, while the wavefronts that fit the chip at
-    // once hold them (64 fp64 matrices of order 16 102 -> 25 us; past that the items only repeat
-    // the levels above them: 500 complex128 of order 14 96 us with 2 each, 109 with 4).  Orders
-    // with more top levels (17 and up in fp64, 15 and up complex) have long items: they take
-    // more until the last round of wavefronts leaves less than 15% of all idle (order 18, 1000
-    // in fp64 1.10 -> 0.55 ms, 20 complex128 2.29 -> 0.10 ms; 1024 complex128 of order 16, which fit
-    // exactly, 0.64 ms with 1 each, 0.79 with 2, 0.77 with 4).
+    // Real matrices with more top levels take at least 4 (their shifted pivots again: 700 of order
+    // 17 304 us with 2, 246 with 4).  More, up to 2^kTopDeferMaxT, where that shortens the launch:
+    // rounds of wavefronts times the time of an item, its chunks and about four chunks' worth of
+    // input, path and drain (64 fp64
+    // matrices of order 16 102 -> 25 us; 1000 of order 18 1.10 -> 0.55 ms; 500 complex128 of order
+    // 14 95 -> 70; 20 of order 18 2.29 -> 0.10 ms.  Not past the full chip: 64 fp64 of order 18
+    // 55 us with 16 each, 67 with 32; 8192 of order 16 0.95 ms with 2 each, 1.0 with 4).
     constexpr int kMost = T < kTopDeferMaxT ? T : kTopDeferMaxT;
     constexpr int64_t kFit = 256 * waves_per_cu(Ly::bytes);
     static_assert(kFit <= kSplitItems, "the queue holds the info codes");
     int levels = 0;
     if (topq && !L.no_split) {
         const int64_t B = L.batch;
-        while (levels < kMost && (1 << levels) < kItems && !(F::kComplex && T > kTopDeferMaxT)) ++levels;
-        if constexpr (T > kTopDeferMaxT) {
-            auto idle = [&](int64_t items) { return (items + kFit - 1) / kFit * kFit * 85 > items * 100; };
-            while (levels < kMost && idle(B << levels) && (B << (levels + 1)) <= split_parts(B)) ++levels;
-        } else {
-            while (levels < kMost && (B << (levels + 1)) <= kFit) ++levels;
-        }
+        constexpr int kLeast = T <= kTopDeferMaxT ? kItems : (F::kComplex ? 1 : 4);
+        auto cost = [&](int l) { return ((B << l) + kFit - 1) / kFit * ((1 << (T - l)) + 4); };
+        while (levels < kMost && (1 << levels) < kLeast) ++levels;
+        for (int l = levels + 1; l <= kMost && (B << l) <= split_parts(B); ++l)
+            if (cost(l) < cost(levels)) levels = l;
     }
     const int split = 1 << levels;
     int* part = topq ? topq + kTopHead + (int64_t)L.topq_cap * (kTopEntryInts + 1) : nullptr;
