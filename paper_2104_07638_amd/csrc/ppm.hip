@@ -239,9 +239,11 @@ __device__ __forceinline__ void gray_steps(const double* __restrict__ Am, double
 // wavefront for 729 x 64 pairs of row sums (12), L product (5) and supersets (14) per Gray step.
 // Two wavefronts per SIMD are asked for: without it the compiler overlaps the steps of orders
 // 10 to 12 until they need 270 registers, and runs one (2048 x 12: 305 us; with it 185, the
-// depth-first supersets before 196).  Three spill: 268 us.
+// depth-first supersets before 196).  Three spill: 268 us.  Orders 9 to 11 are kept at two, where the
+// registers of three cost more than the third brings (2000 x 9 25.1 us, 23.5 at two; 2000 x 10 44.0,
+// 42.6); the others run slower with that bound (8000 x 6 16.1 us, 9.6 without).
 template <int N>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ppm_kernel(const double* __restrict__ A, double* __restrict__ out,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, N >= 9 && N <= 11 ? 2 : 8))) void ppm_kernel(const double* __restrict__ A, double* __restrict__ out,
                                                  int32_t batch, int32_t b0, int n_uniform,
                                                  const int32_t* __restrict__ nv, const int64_t* __restrict__ in_off,
                                                  const int64_t* __restrict__ out_off)
