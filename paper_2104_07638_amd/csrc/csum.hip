@@ -128,21 +128,12 @@ struct CsPlan {
     static constexpr int LB = M < LBW ? M : LBW;
     static constexpr int H = M - LB;
     static constexpr int ROWS = 1 << H;
-    // Byte offset of a row in LDS: rows 16 bytes apart beyond their length, so that lanes reading
-    // different rows at one column spread over the banks; the upper half of 64 rows is shifted
-    // further (with the order of the rows below: 155 cycles a problem of 9 bits for the reads of
-    // all ranks, 186 with even gaps in order of the row numbers, 136 without conflicts; 153 for
-    // 176 with 10 bits).
-    static constexpr int ROW = 8 * ((1 << LB) + (LB > 0 ? 2 : 0));
-    static constexpr int SHIFT = H < 6 ? 0 : (LB == 3 ? 112 : 128);
-    __host__ __device__ static constexpr int row_at(int row) { return row * ROW + (row >> 5) * SHIFT; }
-    static constexpr int ZERO = row_at(ROWS - 1) + ROW;                     // a row of zeros
-    static constexpr int LEN = (ZERO + ROW) / 8;                         // values of a block
+    // Rows in LDS are 16 bytes apart beyond their length, so that lanes reading different rows at
+    // one column spread over the banks.
+    static constexpr int ROW = 8 * ((1 << LB) + (LB > 0 ? 2 : 0));           // bytes from a row to the next
+    static constexpr int LEN = ROWS * ROW / 8;                               // values of a block
     // value x1 of a block
-    __device__ static __forceinline__ int at(int x1)
-    {
-        return (x1 >> LB) * (ROW / 8) + (SHIFT ? (x1 >> (LB + 5)) * (SHIFT / 8) : 0) + (x1 & ((1 << LB) - 1));
-    }
+    __device__ static __forceinline__ int at(int x1) { return (x1 >> LB) * (ROW / 8) + (x1 & ((1 << LB) - 1)); }
 };
 
 // The fixed schedule of a problem: for every rank r >= 1 its rows, G lanes a row (G the largest
@@ -150,20 +141,23 @@ struct CsPlan {
 // step.  The LDS offsets of a pair's two rows are one table entry per step and lane (c' row in
 // the low half, b row in the high half), loaded once at the start of the problem, so a step is
 // its LDS reads and multiply-adds; computing Yh and the offsets from the lane number took twice
-// the instructions of the multiply-adds.  A lane without a pair in a step reads a row of zeros.
+// the instructions of the multiply-adds.  A lane without a pair in a step is masked:
+// reading a row of zeros instead kept the banks busier, and the blocks of 9 bits with such rows took
+// 10.6 KB, 14 wavefronts per CU instead of 16 (8192 problems 35.3 -> 32.7 us).
 // The order of the rows over the lanes is free within a rank: for 64 rows it was searched for the
-// fewest reads of one bank by the 16 lanes that a 16-byte read serves at a time.
+// fewest reads of one bank by the 16 lanes that a 16-byte read serves at a time (121 cycles a
+// problem for the reads of all ranks, 152 in order of the row numbers).
 struct RowOrder {
     uint8_t row[64];
 };
 constexpr RowOrder kRowOrder9 = {
-    {0, 1, 2, 4, 16, 32, 8, 10, 48, 18, 6, 34, 40, 20, 24, 17, 36, 33, 3, 9, 12, 5,
-     28, 44, 22, 11, 37, 14, 52, 26, 21, 13, 42, 41, 25, 35, 19, 38, 7, 56, 50, 49, 46, 43,
-     30, 51, 29, 53, 45, 39, 57, 23, 15, 58, 27, 60, 54, 55, 47, 31, 59, 61, 62, 63}};
+    {0, 16, 1, 4, 8, 2, 32, 33, 5, 20, 9, 10, 12, 34, 36, 17, 24, 3, 6, 48, 40, 18,
+     21, 11, 41, 37, 42, 13, 22, 19, 35, 38, 26, 25, 28, 14, 44, 49, 50, 52, 7, 56, 57, 30,
+     27, 54, 23, 58, 60, 29, 46, 39, 15, 53, 51, 45, 43, 62, 61, 59, 55, 31, 47, 63}};
 constexpr RowOrder kRowOrder10 = {
-    {0, 4, 1, 32, 16, 2, 8, 48, 3, 18, 9, 12, 20, 5, 6, 10, 24, 34, 36, 33, 40, 17,
-     42, 41, 26, 14, 22, 21, 38, 19, 11, 28, 37, 7, 44, 49, 13, 25, 50, 52, 35, 56, 51, 53,
-     54, 57, 46, 60, 58, 43, 39, 15, 23, 29, 27, 30, 45, 62, 55, 61, 59, 47, 31, 63}};
+    {0, 4, 1, 8, 16, 2, 32, 33, 40, 10, 6, 18, 24, 48, 5, 20, 17, 9, 36, 34, 12, 3,
+     13, 28, 42, 49, 38, 14, 26, 21, 44, 37, 19, 22, 11, 25, 41, 50, 52, 56, 35, 7, 29, 60,
+     53, 27, 58, 30, 23, 57, 46, 15, 51, 45, 39, 43, 54, 55, 59, 61, 62, 31, 47, 63}};
 
 template <int M>
 struct OneWave {
@@ -190,6 +184,9 @@ struct OneWave {
         return s;
     }
     static constexpr int total = first(H + 1);
+    static constexpr uint32_t kNone = 0xFFFFFFFFu;
+    // every lane has a pair in step k of rank r
+    static constexpr bool full(int r, int k) { return rows(r) * lanes(r) == kWave && lanes(r) * (k + 1) <= items(r); }
     struct Table {
         uint32_t pair[total > 0 ? total : 1][kWave];
         uint16_t row[H + 1][kWave];      // offset of the lane's row, 0xFFFF: none
@@ -209,7 +206,7 @@ struct OneWave {
             for (int l = 0; l < kWave; ++l) {
                 t.row[r][l] = 0xFFFF;
                 for (int k = 0; r > 0 && k < steps(r); ++k)
-                    t.pair[first(r) + k][l] = (uint32_t)CP::ZERO | ((uint32_t)CP::ZERO << 16);
+                    t.pair[first(r) + k][l] = kNone;
             }
             for (int i = 0; i < CP::ROWS; ++i) {
                 const int x = H < 6 ? i : (M == 9 ? kRowOrder9.row[i] : kRowOrder10.row[i]);
@@ -224,12 +221,12 @@ struct OneWave {
                     int ys = 0;
                     for (int q = 0; q < nl; ++q)
                         if ((s >> q) & 1) ys |= low[q];
-                    t.row[r][o * g + s] = (uint16_t)CP::row_at(x);
+                    t.row[r][o * g + s] = (uint16_t)(x * CP::ROW);
                     int z = 0;
                     for (int k = 0; r > 0 && k < steps(r); ++k, z = (z - hi) & hi) {
                         if (s + g * k >= items(r)) continue;
                         const int y = ys | z;
-                        t.pair[first(r) + k][o * g + s] = (uint32_t)CP::row_at(y) | ((uint32_t)CP::row_at(x ^ y) << 16);
+                        t.pair[first(r) + k][o * g + s] = (uint32_t)(y * CP::ROW) | ((uint32_t)((x ^ y) * CP::ROW) << 16);
                     }
                 }
                 ++o;
@@ -257,6 +254,7 @@ __device__ __forceinline__ void one_wave_ranks(const uint32_t (&pair)[TOT], cons
 #pragma unroll
             for (int k = 0; k < OW::steps(R); ++k) {
                 const uint32_t e = pair[OW::first(R) + k];
+                if (!OW::full(R, k) && e == OW::kNone) continue;
                 double f[W], g[W];
                 ld_row_at<W>(cb, e & 0xFFFFu, f);
                 ld_row_at<W>(bb, e >> 16, g);
@@ -315,10 +313,6 @@ __device__ void cs_problem(const CsArgs& g, int64_t base, int j, bool zero_even,
         for (int k = 0; k < OW::total; ++k) pair[k] = kOneWave<M>.pair[k][tid];
 #pragma unroll
         for (int r = 0; r <= OW::H; ++r) row[r] = kOneWave<M>.row[r][tid];
-        if (tid < OW::W) {
-            lds_c[CP::ZERO / 8 + tid] = 0.0;
-            lds_b[CP::ZERO / 8 + tid] = 0.0;
-        }
         if (j == 0 && !(base & 1)) {
             // rooted problem: a0[x] = a[2x + 1] and b[x] = a[2x] are neighbours, so one 16-byte load
             // per x stages both; the loads of CH entries are issued before their stores (one
