@@ -488,9 +488,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
         un.template lanes<0>(o[0] ? o[0] + ph * kPhase : nullptr, o[1] ? o[1] + ph * kPhase : nullptr);
         un.template lanes<1>(o[2] ? o[2] + ph * kPhase : nullptr, o[3] ? o[3] + ph * kPhase : nullptr);
     };
-    // whether every unit here has a pivot to shift already: its minors are formed elsewhere
+    // whether every unit here has a pivot to shift already: its minors are formed elsewhere (not
+    // those of a non-finite matrix, whatever its tests say: its minors are written here)
     auto lost = [&]() {
-        const uint64_t k = un.bad_rows | ballot(!valid);
+        const uint64_t k = (un.bad_rows & ballot(finite)) | ballot(!valid);
         return (k & 0xFFFFull) && (k & 0xFFFF0000ull) && (k & 0xFFFF00000000ull) && (k >> 48);
     };
     auto below14 = [&](const E(&M14)[14], E mk14) {
