@@ -250,10 +250,10 @@ apm_status apm_xnor_minors(apm_dtype dt, const void *A, const apm_batch *bd, voi
  *   bd      uniform batch, n_uniform = n blocks, 1 <= n <= APM_MAX_N_NAND, no offsets.
  *   out     [B x 3^n]: entry sum_i t_i 3^i is the determinant over the kept rows, with
  *           t_i = 0 (block i left out), 1 (row 2i kept) or 2 (row 2i+1 kept); entry 0 = 1.
- * Matrices with more than six blocks use a workspace of the library per (device, stream):
- * the top-level nodes of the matrices with pivot shifts, which a second launch computes, and
- * a flag per matrix.  It is grown outside stream capture only (a captured call that would
- * grow it returns APM_EUNSUPPORTED).
+ * Matrices with more than six blocks use a workspace of the library per (device, stream), 16
+ * bytes for each 729 minors, for the parts of the tree with pivot shifts, which a second launch
+ * computes.  It is grown outside stream capture only (a captured call that would grow it
+ * returns APM_EUNSUPPORTED).  Threads may share a stream.
  * Returns APM_OK, APM_EINVAL, APM_EUNSUPPORTED, APM_ENOMEM or APM_EDEVICE.
  */
 apm_status apm_nand_minors(apm_dtype dt, const void *A, const apm_batch *bd, void *out, int32_t *info,

@@ -125,35 +125,50 @@ int32_t* get_topq(hipStream_t st, int64_t batch, int32_t* cap_out, TopQueue** q_
     return static_cast<int32_t*>(q.buf);
 }
 
-// Per-(device, stream) workspace of the NAND minors (top-level node matrices, flags), grown on
-// demand outside stream capture; calls on one stream are ordered by the stream.
-struct XorWs {
+// Per-(device, stream) workspace of the NAND minors (nand_parts.h), grown on demand outside
+// stream capture; calls on one stream are ordered by the stream, and `mu` keeps the launches of
+// one call together where threads share a stream.  The head is zero between calls; a call that
+// failed between its launches marks it for re-zeroing (outside capture too).
+struct BlockWs {
     void* buf = nullptr;
     size_t cap = 0;
+    bool dirty = false;
+    std::mutex mu;
 };
-std::map<std::pair<int, hipStream_t>, XorWs> g_xws;
+std::map<std::pair<int, hipStream_t>, BlockWs> g_bws;
 
-apm_status get_xor_ws(hipStream_t st, size_t bytes, void** out)
+apm_status get_block_ws(hipStream_t st, BlockWs** out)
 {
     int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    const hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return from_hip(e);
     std::lock_guard<std::mutex> lk(g_ws_mu);
-    XorWs& w = g_xws[std::make_pair(dev, st)];
+    *out = &g_bws[std::make_pair(dev, st)];   // (nodes of a map stay in place)
+    return APM_OK;
+}
+
+// Room for `bytes` with a zero head; the caller holds w.mu.
+apm_status block_ws_reserve(BlockWs& w, hipStream_t st, size_t bytes)
+{
+    if (w.cap >= bytes && !w.dirty) return APM_OK;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(st, &cs);
+    if (e != hipSuccess) return from_hip(e);
+    if (cs != hipStreamCaptureStatusNone) return APM_EUNSUPPORTED;
     if (w.cap < bytes) {
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        e = hipStreamIsCapturing(st, &cs);
-        if (e != hipSuccess) return from_hip(e);
-        if (cs != hipStreamCaptureStatusNone) return APM_EUNSUPPORTED;
         const size_t cap = bytes > 2 * w.cap ? bytes : 2 * w.cap;
         void* nb = nullptr;
         e = hipMalloc(&nb, cap);
         if (e != hipSuccess) return from_hip(e);
+        std::lock_guard<std::mutex> lk(g_ws_mu);
         retire(w.buf);
         w.buf = nb;
         w.cap = cap;
+        w.dirty = true;
     }
-    *out = w.buf;
+    e = hipMemsetAsync(w.buf, 0, apm::kNandHeadBytes, st);
+    if (e != hipSuccess) return from_hip(e);
+    w.dirty = false;
     return APM_OK;
 }
 
@@ -986,15 +1001,18 @@ apm_status block_minors(int mode, apm_dtype dt, const void* A, const apm_batch* 
     L.batch = bd->batch;
     L.n = bd->n_uniform;
     L.mode = mode;
-    L.ws_stride = apm::xor_ws_elems(L.n, mode);
-    const size_t nodes = (size_t)L.ws_stride * (size_t)bd->batch * (dt == APM_C128 ? 16 : 8);
-    const size_t flags = apm::nand_flags(L.n, mode) ? (size_t)bd->batch * 4 : 0;
-    if (nodes + flags > 0) {
-        apm_status s = get_xor_ws((hipStream_t)stream, nodes + flags, &L.ws);
-        if (s != APM_OK) return s;
-        if (flags) L.flag = reinterpret_cast<int32_t*>(static_cast<char*>(L.ws) + nodes);
-    }
-    return from_hip(apm::xor_launch(L, (hipStream_t)stream));
+    const size_t bytes = mode == 2 ? apm::nand_ws_bytes(L.n, bd->batch) : 0;
+    if (bytes == 0) return from_hip(apm::xor_launch(L, (hipStream_t)stream));
+    BlockWs* w = nullptr;
+    apm_status s = get_block_ws((hipStream_t)stream, &w);
+    if (s != APM_OK) return s;
+    std::lock_guard<std::mutex> lk(w->mu);
+    s = block_ws_reserve(*w, (hipStream_t)stream, bytes);
+    if (s != APM_OK) return s;
+    L.nand = apm::nand_ws_carve(w->buf, L.n, bd->batch);
+    const hipError_t e = apm::xor_launch(L, (hipStream_t)stream);
+    if (e != hipSuccess) w->dirty = true;
+    return from_hip(e);
 }
 
 }  // namespace

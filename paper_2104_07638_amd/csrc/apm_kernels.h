@@ -100,6 +100,20 @@ struct LaunchPerm {
 
 hipError_t perm_launch(const LaunchPerm& L, hipStream_t st);
 
+// Workspace of the NAND minors of 7 blocks and more (nand_parts.h).  The head is zero between
+// calls.
+struct NandWs {
+    int32_t* head;
+    uint64_t* codes;           // a code and a word for each part
+    uint32_t* words;
+    uint32_t* list;            // the marked parts, in `subs` lists of at most `cap`
+    int32_t subs, cap;
+};
+constexpr size_t kNandHeadBytes = 64 * 128 + 64;
+// Bytes for a batch of matrices with n blocks (0: none needed), and its pieces.
+size_t nand_ws_bytes(int n, int64_t batch);
+NandWs nand_ws_carve(void* ws, int n, int64_t batch);
+
 struct LaunchXor {
     int dtype;                 // apm_dtype: R64 or C128
     const void* A;             // [batch][2n][2n]
@@ -107,25 +121,19 @@ struct LaunchXor {
     int32_t* info;
     int32_t batch;
     int n;                     // blocks per matrix
-    void* ws;                  // NAND: top-level node matrices, ws_stride elements per matrix
-    int64_t ws_stride;
-    int32_t* flag;             // NAND, where nand_flags() says so: [batch] workspace
+    NandWs nand;               // NAND, 7 blocks and more
     int mode;                  // 0: XOR minors [batch][2^(n+1) - 2]; 1: XNOR [batch][2^n];
                                // 2: NAND [batch][3^n]
 };
 
-// Elements of top-level workspace per matrix with n blocks (0: none needed), and whether a flag
-// per matrix is needed as well.
-int64_t xor_ws_elems(int n, int mode);
-bool nand_flags(int n, int mode);
 hipError_t xor_launch(const LaunchXor& L, hipStream_t st);
-// The register kernels (4 blocks and more, no workspace).
+// The register kernels (XOR, XNOR: 4 blocks and more; NAND: 7).
 hipError_t xor_row_launch_r64(const LaunchXor& L, hipStream_t st);
 hipError_t xor_row_launch_c128(const LaunchXor& L, hipStream_t st);
 hipError_t xnor_row_launch_r64(const LaunchXor& L, hipStream_t st);
 hipError_t xnor_row_launch_c128(const LaunchXor& L, hipStream_t st);
-hipError_t nand_row_launch_r64(const LaunchXor& L, int32_t* flag, hipStream_t st);
-hipError_t nand_row_launch_c128(const LaunchXor& L, int32_t* flag, hipStream_t st);
+hipError_t nand_row_launch_r64(const LaunchXor& L, hipStream_t st);
+hipError_t nand_row_launch_c128(const LaunchXor& L, hipStream_t st);
 
 // Leading principal minors: [batch][n] of [batch][n][n] (dtype R64 or C128, n <= 32).
 hipError_t lead_launch(int dtype, const void* A, void* out, int32_t* info, int32_t batch, int n, hipStream_t st);

@@ -1,13 +1,12 @@
-// nand_row.h -- NAND minors (Sec. III) with the node matrices in registers, on gfx950, for
-// matrices whose pivots need no shift.
+// nand_row.h -- NAND minors (Sec. III) with the node matrices in registers, on gfx950, without
+// pivot shifts.
 //
 // The ternary tree of xor.hip, with the mapping of xor_row.h: a node of order m <= 16 in a row
 // of 16 lanes (lane j: column j), four units side by side in a wavefront, the order-8 nodes
 // through LDS to one order-6 child per lane.  Every kept row's pivot is put to the tree's shift
 // test, on the same row and column entries.  A shifted pivot needs its subtree corrected
-// afterwards, which this kernel does not do: the matrix is flagged, and the kernel of xor.hip,
-// launched behind this one, does the flagged matrices over.  Propagators away from a zero
-// diagonal shift none.
+// afterwards, which this kernel does not do: it marks the parts below (nand_parts.h), which the
+// launches behind this one form again.
 //
 //   * A unit is a matrix, a choice (left out, first row, second row) for each of its T =
 //     max(0, N - 8) last blocks and, from 8 blocks on, the choice of the block below them: one
@@ -15,22 +14,22 @@
 //   * Top phase: the kept rows are eliminated as in xor_row.h; a left-out block has a zero
 //     pivot row.  The rows that are dropped are followed in the kept columns alone: their
 //     entries there take part in the tests.
-//   * Row phase: for each choice of the next block, two levels to 9 order-8 nodes a unit, 36 in
-//     all (37 KB complex, the LDS of one wavefront per SIMD).
+//   * Row phase: for each choice of the next block (a part each), two levels to 9 order-8 nodes a
+//     unit, 36 in all (37 KB complex, the LDS of one wavefront per SIMD).
 //   * Lane phase: two passes of 54 lanes (18 nodes, 3 children each); a lane's 27 leaves are
 //     staged 9 at a time in the place of the nodes that have been read.
-// Bound by fp64 issue of one wavefront per SIMD.  1024 complex matrices of 10 blocks 1.81 -> 0.39 ms,
-// 176 real ones of 11 3.95 -> 0.085; a batch with flagged matrices also pays for the second
-// launch, at least the time of one matrix there (one zero-diagonal matrix among 1000 of 7 blocks
-// 97 -> 128 us, among 512 of 10 blocks 2205 -> 2490).
+// Bound by fp64 issue of one wavefront per SIMD.  1024 complex matrices of 10 blocks 1.81 ms with
+// one wavefront per matrix in LDS, 0.33 here (no part marked); 512 with a zero diagonal
+// (throughout marked) 2.61 -> 0.78 ms with the launches behind.  One shifted matrix among 1000
+// of 7 blocks 91 -> 76 us, 16000 with a zero diagonal 0.80 -> 0.80 ms.
 #pragma once
+#include "nand_parts.h"
 #include "xor_row.h"
 
 namespace apm {
 namespace nrow {
 
 using xrow::keep_if;
-using xrow::unit_if;
 
 __host__ __device__ constexpr int pow3(int k) { return k <= 0 ? 1 : 3 * pow3(k - 1); }
 constexpr int kNodes = 36;
@@ -59,13 +58,16 @@ struct Unit {
     static constexpr int T = N > 8 ? N - 8 : 0;
     static constexpr int R0 = 2 * (N - T);
     static_assert(N >= 7, "order 14 at least");
-    static constexpr int NPH = N >= 8 ? 9 : 3;   // order-12 nodes of a unit
+    static constexpr int NPH = N >= 8 ? 9 : 3;   // order-12 nodes of a unit: parts (nand_parts.h)
+    static constexpr int L = nand_levels(N);
 
     Lds<F>& sh;
     int l16;
     double tau2;
+    bool finite = true;          // the row's matrix
     double chk_lane = 0.0;       // of the leaves a lane formed (row: lane_row())
-    uint64_t bad_rows = 0;       // lanes (by row) that saw a pivot to shift
+    int first = L;               // the row's first level above its parts with a pivot to shift
+    uint64_t bad_rows = 0;       // a part: lanes (by row) that saw a pivot to shift in the row phase
     uint32_t bad_units = 0;      // the same from the lane phase, a bit per row of lanes
 
     __device__ Unit(Lds<F>& s) : sh(s) {}
@@ -183,9 +185,9 @@ struct Unit {
             multipliers<0, 1>(c, w1);
             // the tests (a left-out block has none)
 #pragma unroll
-            for (int k = 0; k < T; ++k) {
+            for (int k = T - 1; k >= 0; --k) {
                 const double cmax = fmax(cm[k], row_max(F::mag(c[k])));
-                bad_rows |= ballot(digit(path, k) != 0 && small(pm[k], rm[k], cmax));
+                if (digit(path, k) != 0 && small(pm[k], rm[k], cmax)) first = k;
             }
 #pragma unroll
             for (int k = 0; k < T; ++k) sub_rows<0>(M, c[k], w0[k]);
@@ -207,9 +209,10 @@ struct Unit {
     }
 
     // The pivots of both kept children of an order-m node, tested: their reciprocals and the
-    // children's minors, in lanes m - 2 and m - 1.
+    // children's minors, in lanes m - 2 and m - 1; bad[A]: lanes (by row) that saw the pivot of
+    // child A to be shifted.
     template <int m>
-    __device__ __forceinline__ void pivots(const E (&M)[m], E mk, E& mkd, R& rd)
+    __device__ __forceinline__ void pivots(const E (&M)[m], E mk, E& mkd, R& rd, uint64_t (&bad)[2])
     {
         constexpr int mc = m - 2;
         const E d = l16 == mc + 1 ? M[mc + 1] : M[mc];
@@ -222,8 +225,12 @@ struct Unit {
         const double pm = F::mag(d);
         const bool s0 = small(row_bcast<mc>(pm), F::mag(M[mc]), row_bcast<mc>(cm));
         const bool s1 = small(row_bcast<mc + 1>(pm), F::mag(M[mc + 1]), row_bcast<mc + 1>(cm));
-        bad_rows |= ballot(l16 < mc && (s0 || s1));
+        bad[0] = ballot(l16 < mc && s0);
+        bad[1] = ballot(l16 < mc && s1);
     }
+
+    // whether a lane of this lane's row is in the mask
+    __device__ __forceinline__ bool row_in(uint64_t mask) const { return ((mask >> (threadIdx.x & 48)) & 0xFFFF) != 0; }
 
     // The child that keeps row m - 2 + A.
     template <int A, int m>
@@ -266,7 +273,9 @@ struct Unit {
         } else {
             E mkd;
             R rd;
-            pivots(M, mk, mkd, rd);
+            uint64_t bad[2];
+            pivots(M, mk, mkd, rd, bad);
+            bad_rows |= bad[0] | bad[1];
             {
                 E C[m - 2];
                 child<0>(M, C, rd);
@@ -444,12 +453,12 @@ struct Unit {
 };
 
 // Wavefront blockIdx.x: units 4 (blockIdx.x / C) .. + 3 (C = 3 choices of the block below the
-// top ones from 8 blocks on, choice blockIdx.x % 3; else 1).  flag: per matrix, set where a
-// pivot is to be shifted; info and flag are zero beforehand.
+// top ones from 8 blocks on, choice blockIdx.x % 3; else 1).  info gets 0 or -2 from the wavefront
+// of a matrix's first part.
 template <class F, int N, int WAVES>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) void nand_row_kernel(
     const typename F::E* __restrict__ A, typename F::E* __restrict__ out, int32_t* __restrict__ info,
-    int32_t* __restrict__ flag, int64_t units)
+    NandWs ws, int64_t units)
 {
     using E = typename F::E;
     using U = Unit<F, N>;
@@ -469,12 +478,22 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
     U un(sh);
     un.l16 = lane & 15;
     un.tau2 = kDefaultPivTol * kDefaultPivTol;
+    // (the loads of eight entries before their checks: a round trip for each took as long as a part)
     bool fin = true;
-    for (int e = un.l16; e < w * w; e += 16) fin = fin && F::in_finite(A0[e]);
-    const uint64_t nf = ballot(!fin);
-    const bool finite = ((nf >> (lane & 48)) & 0xFFFF) == 0;
+#pragma unroll
+    for (int e0 = 0; e0 < w * w; e0 += 128) {
+        E v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (e0 + 16 * k < w * w) v[k] = load_reg(&A0[min(e0 + 16 * k + un.l16, w * w - 1)]);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (e0 + 16 * k < w * w) fin = fin & F::in_finite(v[k]);
+    }
+    un.finite = !un.row_in(ballot(!fin));
     E M[U::R0], mk = F::one();
-    if (!finite) F::store_nan(&mk, nullptr, 0, false);   // makes every minor NaN
+    if (!un.finite) F::store_nan(&mk, nullptr, 0, false);   // makes every minor NaN
+    if (info && valid && un.l16 == 0 && path == 0 && c1 == 0) info[b] = un.finite ? 0 : -2;
     un.top(A0, path, M, mk);
 
     // the rows' outputs of this wavefront's first phase
@@ -488,67 +507,78 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
         un.template lanes<0>(o[0] ? o[0] + ph * kPhase : nullptr, o[1] ? o[1] + ph * kPhase : nullptr);
         un.template lanes<1>(o[2] ? o[2] + ph * kPhase : nullptr, o[3] ? o[3] + ph * kPhase : nullptr);
     };
-    // whether every unit here has a pivot to shift already: its minors are formed elsewhere (not
-    // those of a non-finite matrix, whatever its tests say: its minors are written here)
-    auto lost = [&]() {
-        const uint64_t k = (un.bad_rows & ballot(finite)) | ballot(!valid);
-        return (k & 0xFFFFull) && (k & 0xFFFF0000ull) && (k & 0xFFFF00000000ull) && (k >> 48);
+    // The words of this wavefront's three parts per row, by its lanes 0 .. 2.  bad: the order-14
+    // node's tests; deep, nonfinite: rows of lanes by part, four bits each.
+    auto tell = [&](const uint64_t (&bad)[2], uint32_t deep, uint32_t nonfinite) {
+        const int c = un.l16, at = 4 * c + (lane >> 4);
+        int first = un.first;
+        if (c && first == U::L && un.row_in(c == 1 ? bad[0] : bad[1])) first = U::L - 1;
+        const bool redo = un.finite && (first < U::L || ((deep >> at) & 1));
+        const bool bad_minor = un.finite && !redo && ((nonfinite >> at) & 1);
+        const uint32_t part = (uint32_t)(u * U::NPH + (N >= 8 ? 3 * c1 : 0) + c);
+        const bool own = valid && c < 3;
+        if (own) ws.words[part] = (uint32_t)first | (redo ? kPartRedo : 0u) | (bad_minor ? kPartBad : 0u);
+        const uint64_t again = ballot(own && redo);
+        if (again) {
+            int at0 = 0;
+            const int sub = (int)blockIdx.x & (ws.subs - 1);
+            if (lane == 0) at0 = atomicAdd(ws.head + sub * kHeadStride, __builtin_popcountll(again));
+            at0 = __builtin_amdgcn_readfirstlane(at0) + sub * ws.cap;
+            if (own && redo) ws.list[at0 + __builtin_popcountll(again & ((uint64_t(1) << lane) - 1))] = part;
+        }
+        if (ballot(own && bad_minor) && lane == 0) atomicAdd(ws.head + kHeadBad, 1);
     };
+    // Whether every row has nothing to write: no such unit, or a pivot to shift (its parts are
+    // formed again; those of a non-finite matrix are not, whatever its tests say)
+    auto lost = [&](bool shift) { return ~ballot(!valid || (un.finite && (un.first < U::L || shift))) == 0; };
     auto below14 = [&](const E(&M14)[14], E mk14) {
         E mkd;
         typename F::R rd;
-        un.pivots(M14, mk14, mkd, rd);
-        if (lost()) return;
+        uint64_t bad[2];
+        un.pivots(M14, mk14, mkd, rd, bad);
+        if (lost(un.row_in(bad[0]) && un.row_in(bad[1]))) return tell(bad, 0xFFFu, 0);
+        uint32_t deep = 0, nonfinite = 0;
 #pragma unroll 1
         for (int c2 = 0; c2 < 3; ++c2) {
             E C[12];
+            un.bad_rows = 0;
             const E mc = un.choose(c2, M14, C, mk14, mkd, rd);
             un.template node<12>(C, mc, 0);
+            un.bad_units = un.nonfinite = 0;
             emit(c2);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if ((un.bad_rows >> (16 * r)) & 0xFFFF) un.bad_units |= 1u << r;
+            deep |= un.bad_units << (4 * c2);
+            nonfinite |= un.nonfinite << (4 * c2);
         }
+        tell(bad, deep, nonfinite);
     };
     if constexpr (N >= 8) {
         E mkd, C[14];
         typename F::R rd;
-        un.pivots(M, mk, mkd, rd);
-        if (!lost()) {
-            const E mc = un.choose(c1, M, C, mk, mkd, rd);
-            below14(C, mc);
-        }
+        uint64_t bad[2];
+        un.pivots(M, mk, mkd, rd, bad);
+        if (c1 && un.row_in(c1 == 1 ? bad[0] : bad[1])) un.first = min(un.first, T);
+        if (lost(false)) return tell(bad, 0xFFFu, 0);
+        const E mc = un.choose(c1, M, C, mk, mkd, rd);
+        below14(C, mc);
     } else {
         below14(M, mk);
-    }
-    // a pivot to shift: the matrix is done over; else its info
-    const bool shift = finite && (((un.bad_rows >> (lane & 48)) & 0xFFFF) || ((un.bad_units >> (lane >> 4)) & 1));
-    if (valid && un.l16 == 0) {
-        if (shift) flag[b] = 1;
-        const int code = !finite ? -2 : ((un.nonfinite >> (lane >> 4)) & 1) ? -3 : 0;
-        if (info && code) atomicMin(&info[b], code);
-    }
-}
-
-__global__ static void nand_clear_kernel(int32_t* info, int32_t* flag, int32_t batch)
-{
-    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i < batch) {
-        flag[i] = 0;
-        if (info) info[i] = 0;
     }
 }
 
 template <class F, int WAVES, int N>
-hipError_t launch_n(const LaunchXor& L, int32_t* flag, hipStream_t st)
+hipError_t launch_n(const LaunchXor& L, hipStream_t st)
 {
     if constexpr (N > 13) {
         return hipErrorInvalidValue;
     } else {
-        if (L.n != N) return launch_n<F, WAVES, N + 1>(L, flag, st);
+        if (L.n != N) return launch_n<F, WAVES, N + 1>(L, st);
         const int64_t units = (int64_t)L.batch * pow3(Unit<F, N>::T);
-        hipLaunchKernelGGL(nand_clear_kernel, dim3((unsigned)((L.batch + 255) / 256)), dim3(256), 0, st, L.info, flag,
-                           L.batch);
-        const int64_t grid = (units + 3) / 4 * (N >= 8 ? 3 : 1);
+        const int64_t grid = nand_row_waves(N, L.batch);
         hipLaunchKernelGGL((nand_row_kernel<F, N, WAVES>), dim3((unsigned)grid), dim3(64), 0, st,
-                           static_cast<const typename F::E*>(L.A), static_cast<typename F::E*>(L.out), L.info, flag,
+                           static_cast<const typename F::E*>(L.A), static_cast<typename F::E*>(L.out), L.info, L.nand,
                            units);
         return hipGetLastError();
     }

@@ -3,9 +3,9 @@
 
 namespace apm {
 
-hipError_t nand_row_launch_c128(const LaunchXor& L, int32_t* flag, hipStream_t st)
+hipError_t nand_row_launch_c128(const LaunchXor& L, hipStream_t st)
 {
-    return nrow::launch_n<FC128, 1, 7>(L, flag, st);
+    return nrow::launch_n<FC128, 1, 7>(L, st);
 }
 
 }  // namespace apm

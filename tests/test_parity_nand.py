@@ -89,3 +89,122 @@ def test_non_finite_among_shifted(apm, oracle_mod, n, B, cplx):
     for b in (0, B - 1):
         assert info[b] > 0
         _check(oracle_mod, got[b], A[b], (n, cplx, b))
+
+
+@pytest.mark.parametrize("n", [7, 8, 9, 10, 11])
+def test_shifts_at_single_places(apm, oracle_mod, n):
+    """Matrix b < 2 n has one zero on its diagonal, in row b: that pivot is shifted in the nodes
+    that leave every later block out (a level above the parts, inside a part's rows or in its
+    lanes, by the block), and most of the tree has no shift.  Then matrices with two such rows,
+    of neighbouring and of distant blocks, and a plain one: every entry, and which matrices
+    count shifts."""
+    rng = np.random.default_rng(3200 + n)
+    pairs = [(2 * n - 1, 2 * n - 3), (2 * n - 2, 2 * n - 1), (2 * n - 4, 1), (3, 0), (2 * n - 1, 6)]
+    for cplx in (False, True):
+        A = _matrices(rng, 2 * n + len(pairs) + 1, n, cplx, 12.0)
+        for b in range(2 * n):
+            A[b, b, b] = 0.0
+        for k, (r, s) in enumerate(pairs):
+            A[2 * n + k, r, r] = A[2 * n + k, s, s] = 0.0
+        got, info = _nand(apm, A)
+        # the rows of the first block are the tree's leaves: a leaf's pivot is not shifted
+        first = np.arange(len(A)) < 2
+        assert np.all(info >= 0) and np.all(info[:-1][~first[:-1]] > 0), info
+        for b in range(len(A)) if n < 10 else (1, 2, 5, 10, 2 * n - 1, 2 * n, 2 * n + 2, 2 * n + 4):
+            _check(oracle_mod, got[b], A[b], (n, cplx, b))
+
+
+def test_every_batch_size_same_bits(apm):
+    """A batch with more parts than one pass of the second launch looks at (64 times its grid),
+    made of eight matrices over and over (plain, shifted throughout, at one place, non-finite),
+    gives the bits of the eight alone, info included; so does the call without info."""
+    import torch
+    n, rep = 8, 3660
+    rng = np.random.default_rng(3300)
+    A = _matrices(rng, 8, n, False, 12.0)
+    _zero_diagonal(A, 1)
+    _zero_diagonal(A, 6)
+    for b, r in ((2, 15), (3, 9), (4, 4)):
+        A[b, r, r] = 0.0
+    A[5, 3, 2] = np.nan
+    dA = torch.from_numpy(A).cuda()
+    want, info = apm.nand_minors(dA)
+    out = torch.full((8 * rep, 3 ** n), 7.0, dtype=torch.float64, device="cuda")
+    big, binfo = apm.nand_minors(dA.repeat(rep, 1, 1), out=out)
+    torch.cuda.synchronize()
+    assert info.tolist()[5] == -2 and all(info[b] > 0 for b in (1, 2, 3, 4, 6)) and info[0] == info[7] == 0
+    assert torch.equal(binfo.view(rep, 8), info.expand(rep, 8))
+    assert torch.equal(big.view(torch.int64).view(rep, 8, -1), want.view(torch.int64).expand(rep, 8, 3 ** n))
+    out2 = torch.full_like(want, 7.0)
+    assert apm.apm_nand_minors(apm.APM_R64, apm._ptr(dA), apm.make_batch(8, n), apm._ptr(out2), None,
+                               apm._stream(None)) == apm.APM_OK
+    assert torch.equal(out2.view(torch.int64), want.view(torch.int64))
+
+
+@pytest.mark.parametrize("n", [7, 10])
+def test_captured_with_shifts(apm, n):
+    """A captured call (its workspace sized by an eager one) replayed on new inputs, plain and
+    shifted in turn, with eager work between, equals the eager call."""
+    import torch
+    rng = np.random.default_rng(3400 + n)
+    plain = _matrices(rng, 5, n, True, 12.0)
+    mixed = plain.copy()
+    _zero_diagonal(mixed, 1)
+    mixed[3, 2 * n - 1, 2 * n - 1] = 0.0
+    src = [torch.from_numpy(x).cuda() for x in (plain, mixed)]
+    want = [apm.nand_minors(s) for s in src]
+    dA, out, info = src[0].clone(), torch.zeros_like(want[0][0]), torch.zeros_like(want[0][1])
+    bd = apm.make_batch(5, n)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    args = (apm.APM_C128, apm._ptr(dA), bd, apm._ptr(out), apm._ptr(info))
+    with torch.cuda.stream(side):
+        assert apm.apm_nand_minors(*args, apm._stream(None)) == apm.APM_OK
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        assert apm.apm_nand_minors(*args, apm._stream(None)) == apm.APM_OK
+    for k in (1, 0, 1, 1, 0):
+        dA.copy_(src[k])
+        out.fill_(7.0)
+        g.replay()
+        eager, _ = apm.nand_minors(src[1 - k])
+        torch.cuda.synchronize()
+        assert torch.equal(torch.view_as_real(out), torch.view_as_real(want[k][0])) and torch.equal(info, want[k][1])
+        assert torch.equal(torch.view_as_real(eager), torch.view_as_real(want[1 - k][0]))
+
+
+def test_threads_on_one_stream(apm):
+    """Four threads call on the same stream (a call is three launches over one workspace), each
+    with its own plain and shifted matrices of another size: the results of the calls alone."""
+    import threading
+    import torch
+    rng = np.random.default_rng(3500)
+    jobs = []
+    for t, (n, B) in enumerate([(7, 40), (8, 9), (7, 3), (9, 5)]):
+        A = _matrices(rng, B, n, bool(t & 1), 12.0)
+        _zero_diagonal(A, t % B)
+        A[-1, 2 * n - 1, 2 * n - 1] = 0.0
+        jobs.append(torch.from_numpy(A).cuda())
+    want = [apm.nand_minors(A) for A in jobs]
+    got = [[] for _ in jobs]
+    torch.cuda.synchronize()
+    start = threading.Barrier(len(jobs))
+
+    def work(t):
+        start.wait()
+        for _ in range(30):
+            got[t].append(apm.nand_minors(jobs[t]))
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(len(jobs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for (m, i), res in zip(want, got):
+        assert len(res) == 30
+        for m1, i1 in res:
+            assert torch.equal(i, i1)
+            assert torch.equal(m.view(torch.float64) if not m.is_complex() else torch.view_as_real(m),
+                               m1 if not m.is_complex() else torch.view_as_real(m1))
