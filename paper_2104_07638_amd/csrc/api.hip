@@ -92,36 +92,48 @@ apm_status get_workspace(int64_t batch, int32_t** counter, int32_t** order, int6
 // Per-(device, stream) queue of deferred top-level corrections for uniform batches.  Each
 // use leaves it zeroed; a call that failed after using it marks it for re-zeroing.  It is
 // only (re)allocated or re-zeroed outside stream capture: a captured call that would need
-// that runs the corrections inside the minors kernel instead.
+// that runs the corrections inside the minors kernel instead.  `mu` keeps the launches of one
+// call together where threads share a stream: the corrections of a call take every matrix
+// listed, by the order of their own call.
 struct TopQueue {
     void* buf = nullptr;
     int64_t cap = 0;
     bool dirty = false;
+    std::mutex mu;
 };
 std::map<std::pair<int, hipStream_t>, TopQueue> g_topq;
 
-int32_t* get_topq(hipStream_t st, int64_t batch, int32_t* cap_out, TopQueue** q_out)
+TopQueue* find_topq(hipStream_t st)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return nullptr;
     std::lock_guard<std::mutex> lk(g_ws_mu);
-    TopQueue& q = g_topq[std::make_pair(dev, st)];
+    return &g_topq[std::make_pair(dev, st)];   // (nodes of a map stay in place)
+}
+
+// The zeroed queue with room for `batch` matrices, or NULL; the caller holds q.mu.
+int32_t* topq_reserve(TopQueue& q, hipStream_t st, int64_t batch, int32_t* cap_out)
+{
     if (q.cap < batch || q.dirty) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return nullptr;
         if (q.cap < batch) {
             const int64_t cap = grown(q.cap, batch, 4096);
             void* nb = nullptr;
-            if (hipMalloc(&nb, (size_t)apm::fpm_topq_bytes(cap)) != hipSuccess) return nullptr;
+            if (hipMalloc(&nb, (size_t)apm::fpm_topq_bytes(cap)) != hipSuccess) {
+                (void)hipGetLastError();   // the call runs without a queue: not its error
+                return nullptr;
+            }
+            std::lock_guard<std::mutex> lk(g_ws_mu);
             retire(q.buf);
             q.buf = nb;
             q.cap = cap;
+            q.dirty = true;
         }
         if (hipMemsetAsync(q.buf, 0, (size_t)apm::fpm_topq_bytes(q.cap), st) != hipSuccess) return nullptr;
         q.dirty = false;
     }
     *cap_out = (int32_t)q.cap;
-    *q_out = &q;
     return static_cast<int32_t*>(q.buf);
 }
 
@@ -699,17 +711,19 @@ apm_status apm_all_minors(apm_dtype dt, const void* A, const apm_batch* bd, void
     apm_status s = minors_args(dt, A, bd, minors, exp, info, opt, &L, &noop);
     if (s != APM_OK || noop) return s;
     TopQueue* tq = nullptr;
+    std::unique_lock<std::mutex> lk;
     if (bd->n_uniform == 0) {
         s = get_workspace(bd->batch, &L.counter, &L.order, &L.ioff_ws, &L.ooff_ws, &L.n_workers);
         if (s != APM_OK) return s;
     } else if (bd->batch <= INT32_MAX / 2) {
-        L.topq = get_topq((hipStream_t)stream, bd->batch, &L.topq_cap, &tq);
+        tq = find_topq((hipStream_t)stream);
+        if (tq) {
+            lk = std::unique_lock<std::mutex>(tq->mu);
+            L.topq = topq_reserve(*tq, (hipStream_t)stream, bd->batch, &L.topq_cap);
+        }
     }
     const hipError_t e = apm::fpm_launch(L, (hipStream_t)stream);
-    if (e != hipSuccess && tq) {
-        std::lock_guard<std::mutex> lk(g_ws_mu);
-        tq->dirty = true;
-    }
+    if (e != hipSuccess && L.topq) tq->dirty = true;
     return from_hip(e);
 }
 
