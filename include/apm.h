@@ -344,9 +344,9 @@ void apm_minors_k0_mixed(apm_dtype dt, int32_t *k0_small, int32_t *k0_large);
  * minors, or those of the two mixed-order kernels (timing every instantiated order first
  * with APM_PLAN_AUTOTUNE, as apm_autotune_minors / apm_autotune_minors_mixed do, when
  * neither the process nor the tuning cache has a value for that dtype and order yet), and
- * records the whole launch sequence once into a HIP graph on a private stream.
- * apm_plan_launch then enqueues that graph on the caller's stream, or, for a plan of up to
- * eight kernels, the kernels one by one (which costs less), with results bit-identical to the
+ * records the whole launch sequence once on a private stream.  apm_plan_launch then enqueues
+ * it as one HIP graph on the caller's stream, or, for a plan of up to eight kernels (which
+ * keeps no graph), the kernels one by one, which costs less, with results bit-identical to the
  * direct calls.  With APM_PLAN_EAGER the plan records nothing and each launch enqueues the
  * kernels one by one (same results).
  *
@@ -411,8 +411,9 @@ apm_status apm_plan_create(const apm_plan_desc *d, apm_plan **out);
 apm_status apm_plan_launch(apm_plan *p, apm_stream stream);
 
 /* Lane-subtree order pinned in a minors or CDET plan (for a mixed-order batch: that of the
- * orders other than 14..16; 0 for other plans), and whether the plan holds a graph (1) or launches
- * eagerly (0).  Host-only; -1 for a NULL plan. */
+ * orders other than 14..16; 0 for other plans), and whether the launch sequence was recorded at
+ * create (1: launches replay it as a graph or, for up to eight kernels, one by one) or not (0:
+ * APM_PLAN_EAGER, or nothing to launch).  Host-only; -1 for a NULL plan. */
 int32_t apm_plan_k0(const apm_plan *p);
 int32_t apm_plan_graphed(const apm_plan *p);
 

@@ -514,7 +514,8 @@ def decode_scaled(m, e):
 
 class Plan:
     """An ``apm_plan``: one operation (or the CDet pipeline) bound to fixed device tensors,
-    recorded once into a HIP graph by the library and enqueued by ``launch()``.
+    recorded once by the library and enqueued by ``launch()``, as one HIP graph or, for up to
+    eight kernels, one by one (``graphed`` says that it was recorded, not which).
 
     Build one with the ``plan_*`` helpers below; the plan keeps references to every tensor
     it names, so they stay allocated (their values may change between launches)."""

@@ -506,10 +506,10 @@ struct apm_plan {
     void* ws = nullptr;           // counter | order | ioff | ooff | deferred-correction queue
     size_t ws_bytes = 0;
     bool dirty = false;           // an eager launch failed after the queue was used
-    hipStream_t ps = nullptr;     // private stream the graph is recorded on
-    hipGraph_t g = nullptr;
+    hipStream_t ps = nullptr;     // private stream the launch sequence is recorded on
+    bool recorded = false;
+    hipGraph_t g = nullptr;       // NULL for few kernels, which are launched one by one
     hipGraphExec_t ge = nullptr;
-    bool few = false;             // few kernels: launched one by one
 };
 
 namespace {
@@ -1129,12 +1129,15 @@ apm_status apm_plan_create(const apm_plan_desc* d, apm_plan** out)
         }
         size_t nodes = 0;
         if (e == hipSuccess) e = hipGraphGetNodes(p->g, nullptr, &nodes);
-        p->few = nodes <= kFewKernels;
-        if (e == hipSuccess) e = hipGraphInstantiate(&p->ge, p->g, nullptr, nullptr, 0);
-        if (e != hipSuccess) {
-            p->ge = nullptr;
-            s = from_hip(e);
+        if (e == hipSuccess && nodes > kFewKernels) {
+            e = hipGraphInstantiate(&p->ge, p->g, nullptr, nullptr, 0);
+            if (e != hipSuccess) p->ge = nullptr;
+        } else if (e == hipSuccess) {
+            e = hipGraphDestroy(p->g);
+            p->g = nullptr;
         }
+        p->recorded = e == hipSuccess;
+        if (e != hipSuccess) s = from_hip(e);
     }
     if (s != APM_OK) {
         plan_free(p);
@@ -1153,7 +1156,7 @@ apm_status apm_plan_launch(apm_plan* p, apm_stream stream)
     if (e != hipSuccess) return from_hip(e);
     if (dev != p->dev) return APM_EINVAL;
     const hipStream_t st = (hipStream_t)stream;
-    if (p->ge && !p->few) return from_hip(hipGraphLaunch(p->ge, st));
+    if (p->ge) return from_hip(hipGraphLaunch(p->ge, st));
     if (p->dirty) {
         // a failed launch may have left deferred corrections queued: clear them (outside capture
         // only; a plan is not recorded while in this state)
@@ -1172,7 +1175,7 @@ apm_status apm_plan_launch(apm_plan* p, apm_stream stream)
 
 int32_t apm_plan_k0(const apm_plan* p) { return p ? p->k0 : -1; }
 
-int32_t apm_plan_graphed(const apm_plan* p) { return p ? (p->ge != nullptr ? 1 : 0) : -1; }
+int32_t apm_plan_graphed(const apm_plan* p) { return p ? (p->recorded ? 1 : 0) : -1; }
 
 void apm_plan_destroy(apm_plan* p) { plan_free(p); }
 
