@@ -87,15 +87,18 @@ struct Unit {
         return (path / w) % 3;
     }
 
-    // c[k2] -= c[K] (entry of the scaled pivot row K in block k2's kept column), K < k2
+    // c[k2] -= c[K] (entry of the scaled pivot row K in block k2's kept column), K < k2; zero
+    // where block K is left out (in[K]): its column may have overflowed, and its pivot row of
+    // zeros would make that a NaN
     template <int K, int K2>
-    __device__ __forceinline__ void multipliers(E (&c)[T > 0 ? T : 1], const E (&w1)[T > 0 ? T : 1])
+    __device__ __forceinline__ void multipliers(E (&c)[T > 0 ? T : 1], const E (&w1)[T > 0 ? T : 1], const int (&in)[T > 0 ? T : 1])
     {
+        if constexpr (K2 == K + 1) c[K] = keep_if(in[K], c[K]);
         if constexpr (K2 < T) {
             c[K2] = F::upd(c[K2], c[K], row_bcast<2 * K2>(w1[K]));
-            multipliers<K, K2 + 1>(c, w1);
-        } else if constexpr (K + 2 < T) {
-            multipliers<K + 1, K + 2>(c, w1);
+            multipliers<K, K2 + 1>(c, w1, in);
+        } else if constexpr (K + 1 < T) {
+            multipliers<K + 1, K + 2>(c, w1, in);
         }
     }
 
@@ -117,14 +120,15 @@ struct Unit {
     // decided ones a1; cm[J]: largest entry met in pivot column J
     template <int J, int K, bool Both>
     __device__ __forceinline__ void apply(E& a0, E& a1, const E (&w0)[T > 0 ? T : 1], const E (&w1)[T > 0 ? T : 1],
-                                          double (&cm)[T > 0 ? T : 1])
+                                          double (&cm)[T > 0 ? T : 1], const int (&in)[T > 0 ? T : 1])
     {
         if constexpr (J < K) {
-            const E c = row_bcast<2 * J>(a1);
+            E c = row_bcast<2 * J>(a1);
             cm[J] = fmax(cm[J], F::mag(c));
+            c = keep_if(in[J], c);
             if constexpr (Both) a0 = F::upd(a0, c, w0[J]);
             a1 = F::upd(a1, c, w1[J]);
-            apply<J + 1, K, Both>(a0, a1, w0, w1, cm);
+            apply<J + 1, K, Both>(a0, a1, w0, w1, cm, in);
         }
     }
 
@@ -133,22 +137,21 @@ struct Unit {
     template <int K>
     __device__ __forceinline__ void pivot_rows(E (&w0)[T > 0 ? T : 1], E (&w1)[T > 0 ? T : 1], E (&x1)[T > 0 ? T : 1],
                                                double (&cm)[T > 0 ? T : 1], double (&rm)[T > 0 ? T : 1],
-                                               double (&pm)[T > 0 ? T : 1], int path, E& mk)
+                                               double (&pm)[T > 0 ? T : 1], const int (&in)[T > 0 ? T : 1], E& mk)
     {
         if constexpr (K < T) {
-            const int in = -(int)(digit(path, K) != 0);
             E a0 = w0[K], a1 = w1[K], o1 = x1[K];
-            apply<0, K, true>(a0, a1, w0, w1, cm);
-            apply<0, K, false>(o1, o1, w1, w1, cm);
+            apply<0, K, true>(a0, a1, w0, w1, cm, in);
+            apply<0, K, false>(o1, o1, w1, w1, cm, in);
             const E pv = row_bcast<2 * K>(a1);
             const double m0 = F::mag(a0), m1 = F::mag(a1);
             rm[K] = row_max(l16 > 2 * K + 1 && l16 < 2 * T ? fmax(m0, m1) : m0);
             pm[K] = F::mag(pv);
-            if (in) mk = F::bmul(mk, pv, 0);
+            if (in[K]) mk = F::bmul(mk, pv, 0);
             const R r = F::recip(pv);
-            w0[K] = keep_if(in, F::rowscale(a0, r));
-            w1[K] = keep_if(in, F::rowscale(a1, r));
-            pivot_rows<K + 1>(w0, w1, x1, cm, rm, pm, path, mk);
+            w0[K] = keep_if(in[K], F::rowscale(a0, r));
+            w1[K] = keep_if(in[K], F::rowscale(a1, r));
+            pivot_rows<K + 1>(w0, w1, x1, cm, rm, pm, in, mk);
         }
     }
 
@@ -179,15 +182,19 @@ struct Unit {
             for (int i = 0; i < R0; ++i) M[i] = load_reg(&A0[i * w + l16]);
             __builtin_amdgcn_sched_barrier(0);
             double cm[T], rm[T], pm[T];
+            int in[T];                             // all ones where block k is kept
 #pragma unroll
-            for (int k = 0; k < T; ++k) cm[k] = 0.0;
-            pivot_rows<0>(w0, w1, x1, cm, rm, pm, path, mk);
-            multipliers<0, 1>(c, w1);
+            for (int k = 0; k < T; ++k) {
+                cm[k] = 0.0;
+                in[k] = -(int)(digit(path, k) != 0);
+            }
+            pivot_rows<0>(w0, w1, x1, cm, rm, pm, in, mk);
+            multipliers<0, 1>(c, w1, in);
             // the tests (a left-out block has none)
 #pragma unroll
             for (int k = T - 1; k >= 0; --k) {
                 const double cmax = fmax(cm[k], row_max(F::mag(c[k])));
-                if (digit(path, k) != 0 && small(pm[k], rm[k], cmax)) first = k;
+                if (in[k] && small(pm[k], rm[k], cmax)) first = k;
             }
 #pragma unroll
             for (int k = 0; k < T; ++k) sub_rows<0>(M, c[k], w0[k]);

@@ -208,3 +208,34 @@ def test_threads_on_one_stream(apm):
             assert torch.equal(i, i1)
             assert torch.equal(m.view(torch.float64) if not m.is_complex() else torch.view_as_real(m),
                                m1 if not m.is_complex() else torch.view_as_real(m1))
+
+
+@pytest.mark.parametrize("n,cplx", [(10, False), (10, True), (11, False)])
+def test_left_out_columns_do_not_enter(apm, oracle_mod, n, cplx):
+    """Finite minors next to an overflow in a column that they do not have: row 2n - 2 has a pivot
+    of 1e160 and 1e250 in block n - 2's first column, row 0 has 1e250 in the pivot's column, so the
+    update of (row 0, that column) overflows.  The rest of row 2n - 2 is 1e-90, so that the
+    updates of the other columns are of order 1 and no pivot is shifted there.  (The pivot's
+    own square and its row and column scale both overflow in the shift test, which then shifts
+    nothing.)  With block n - 2 left out, every minor is 1e160 times an ordinary one."""
+    rng = np.random.default_rng(3600 + n)
+    A = _matrices(rng, 1, n, cplx, 12.0)
+    p, k = 2 * n - 2, 2 * n - 4
+    A[0, p] *= 1e-90
+    A[0, p, p] = 1e160
+    A[0, p, k] = A[0, 0, p] = 1e250
+    got, _ = _nand(apm, A)
+    ref = oracle_mod.nand_minors(A)[0]
+    digits = (np.arange(3 ** n)[:, None] // 3 ** np.arange(n)[None, :]) % 3
+    sel = (digits[:, n - 1] == 1) & (digits[:, n - 2] == 0)
+    # the Schur complement over the pivot, whose rows bound the minors
+    S = A[0].copy()
+    S[:, k] = 0.0
+    S = S - np.outer(S[:, p] / 1e160, S[p])
+    ln = np.log(np.linalg.norm(np.delete(S, p, axis=1), axis=1) + 1e-300)
+    lt = np.stack([np.zeros(n), ln[0::2], ln[1::2]], axis=1)
+    lt[n - 1, 1] = 0.0
+    H = np.exp(lt[np.arange(n)[None, :], digits].sum(axis=1)[sel])
+    assert np.all(np.isfinite(ref[sel])) and np.all(np.isfinite(got[0][sel])), int(np.sum(~np.isfinite(got[0][sel])))
+    e = metrics.mixed_err(got[0][sel] / 1e160, ref[sel] / 1e160, H)
+    assert e.max() <= GATE, float(e.max())
