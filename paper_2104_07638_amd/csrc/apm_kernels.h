@@ -54,6 +54,10 @@ int64_t fpm_topq_bytes_unsplit(int64_t batch);
 
 hipError_t fpm_launch(const LaunchMinors& L, hipStream_t st);
 
+// Compute units of an MI355X, for the rules that split a launch over the chip (persistent grids
+// ask the device).
+constexpr int64_t kCus = 256;
+
 // Lane-subtree order per (dtype, order): tuned values installed by the autotuner
 // (0 = none), the instantiated range of a dtype, and the synthetic tuning input.
 int tuned_k0(int dtype, int n);

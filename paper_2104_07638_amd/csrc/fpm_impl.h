@@ -1064,7 +1064,7 @@ hipError_t launch_uniform(const LaunchMinors& L, hipStream_t st)
     // 14 95 -> 70; 20 of order 18 2.29 -> 0.10 ms.  Not past the full chip: 64 fp64 of order 18
     // 55 us with 16 each, 67 with 32; 8192 of order 16 0.95 ms with 2 each, 1.0 with 4).
     constexpr int kMost = T < kTopDeferMaxT ? T : kTopDeferMaxT;
-    constexpr int64_t kFit = 256 * waves_per_cu(Ly::bytes);
+    constexpr int64_t kFit = kCus * waves_per_cu(Ly::bytes);
     static_assert(kFit <= kSplitItems, "the queue holds the info codes");
     int levels = 0;
     if (topq && !L.no_split) {

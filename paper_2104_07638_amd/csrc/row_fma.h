@@ -445,20 +445,6 @@ __device__ __forceinline__ void row_child2(cd& c0, cd& c1, cd& c2, cd& c3, cd a0
 
 // a[r] -= (lane P + r of s) w
 template <int P>
-__device__ __forceinline__ void row_sub_lanes(double& a0, double& a1, double& a2, double& a3, double& a4, double& a5, double s, double w)
-{
-    asm("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, -%6, %7" APM_BC(8)
-        "v_fmac_f64_dpp %1, -%6, %7" APM_BC(9)
-        "v_fmac_f64_dpp %2, -%6, %7" APM_BC(10)
-        "v_fmac_f64_dpp %3, -%6, %7" APM_BC(11)
-        "v_fmac_f64_dpp %4, -%6, %7" APM_BC(12)
-        "v_fmac_f64_dpp %5, -%6, %7" APM_BC(13)
-        : "+&v"(a0), "+&v"(a1), "+&v"(a2), "+&v"(a3), "+&v"(a4), "+&v"(a5)
-        : "v"(s), "v"(w), "n"(P + 0), "n"(P + 1), "n"(P + 2), "n"(P + 3), "n"(P + 4), "n"(P + 5));
-}
-
-template <int P>
 __device__ __forceinline__ void row_sub_lanes(double& a0, double& a1, double& a2, double& a3, double& a4, double& a5, double& a6, double& a7, double s, double w)
 {
     asm("s_nop 1\n\t"
@@ -472,22 +458,6 @@ __device__ __forceinline__ void row_sub_lanes(double& a0, double& a1, double& a2
         "v_fmac_f64_dpp %7, -%8, %9" APM_BC(17)
         : "+&v"(a0), "+&v"(a1), "+&v"(a2), "+&v"(a3), "+&v"(a4), "+&v"(a5), "+&v"(a6), "+&v"(a7)
         : "v"(s), "v"(w), "n"(P + 0), "n"(P + 1), "n"(P + 2), "n"(P + 3), "n"(P + 4), "n"(P + 5), "n"(P + 6), "n"(P + 7));
-}
-
-template <int P>
-__device__ __forceinline__ void row_sub_lanes(cd& a0, cd& a1, cd s, cd w)
-{
-    asm("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, %5, %7" APM_BC(8)
-        "v_fmac_f64_dpp %2, %5, %7" APM_BC(9)
-        "v_fmac_f64_dpp %1, -%5, %6" APM_BC(8)
-        "v_fmac_f64_dpp %3, -%5, %6" APM_BC(9)
-        "v_fmac_f64_dpp %0, -%4, %6" APM_BC(8)
-        "v_fmac_f64_dpp %2, -%4, %6" APM_BC(9)
-        "v_fmac_f64_dpp %1, -%4, %7" APM_BC(8)
-        "v_fmac_f64_dpp %3, -%4, %7" APM_BC(9)
-        : "+&v"(a0.x), "+&v"(a0.y), "+&v"(a1.x), "+&v"(a1.y)
-        : "v"(s.x), "v"(s.y), "v"(w.x), "v"(w.y), "n"(P + 0), "n"(P + 1));
 }
 
 template <int P>

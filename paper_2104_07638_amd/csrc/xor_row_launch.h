@@ -23,7 +23,7 @@ hipError_t launch_n(const LaunchXor& L, hipStream_t st)
         // Wavefronts per matrix: as many as bring the launch to four per wavefront slot (the
         // units share nothing, so a split costs only the input check of each wavefront).
         int split = 1;
-        while (4 * split < (1 << T) && (int64_t)L.batch * split < 4096 * WAVES) split *= 2;
+        while (4 * split < (1 << T) && (int64_t)L.batch * split < 16 * kCus * WAVES) split *= 2;
         const int per_wave = T >= 2 ? (1 << T) / split : 4;
         const int64_t grid = (units + per_wave - 1) / per_wave;
         if (split > 1 && L.info)
