@@ -13,7 +13,7 @@
 // up to a multiple of 4 (the kernel's compile-time order R); the rows and columns past n repeat
 // the last one and influence none before them.
 // Bound by the input (8 n^2 bytes a matrix) and the chain of n pivots.  8192 matrices of order
-// 16: one wavefront per matrix with the matrix in LDS 31 us, this 7 us (2.5 TB/s).
+// 16: one wavefront per matrix with the matrix in LDS 31 us, this 5.9 us (3.0 TB/s).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

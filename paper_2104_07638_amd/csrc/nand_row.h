@@ -19,7 +19,7 @@
 //   * Lane phase: two passes of 54 lanes (18 nodes, 3 children each); a lane's 27 leaves are
 //     staged 9 at a time in the place of the nodes that have been read.
 // Bound by fp64 issue of one wavefront per SIMD.  1024 complex matrices of 10 blocks 1.81 ms with
-// one wavefront per matrix in LDS, 0.33 here (no part marked); 512 with a zero diagonal
+// one wavefront per matrix in LDS, 0.30 here (no part marked); 512 with a zero diagonal
 // (throughout marked) 2.61 -> 0.78 ms with the launches behind.  One shifted matrix among 1000
 // of 7 blocks 91 -> 76 us, 16000 with a zero diagonal 0.80 -> 0.80 ms.
 #pragma once

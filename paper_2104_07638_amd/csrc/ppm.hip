@@ -235,8 +235,9 @@ __device__ __forceinline__ void gray_steps(const double* __restrict__ Am, double
     }
 }
 
-// Bound by fp64 issue: 78% of the vector cycles are busy at order 12, 3000 instructions per
-// wavefront for 729 x 64 pairs of row sums (12), L product (5) and supersets (14) per Gray step.
+// Bound by the fp64 chains of two wavefronts per SIMD: vector instructions issue at 56% of the chip's
+// rate at order 12, 2900 a wavefront (729 pairs of lanes' subsets a matrix, each with row sums (12),
+// L product (5) and supersets (14) per Gray step; lanes of the same Tl1 repeat each other's sums).
 // Two wavefronts per SIMD are asked for: without it the compiler overlaps the steps of orders
 // 10 to 12 until they need 270 registers, and runs one (2048 x 12: 305 us; with it 185, the
 // depth-first supersets before 196).  Three spill: 268 us.  Orders 9 to 11 are kept at two, where the
