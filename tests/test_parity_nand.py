@@ -239,3 +239,31 @@ def test_left_out_columns_do_not_enter(apm, oracle_mod, n, cplx):
     assert np.all(np.isfinite(ref[sel])) and np.all(np.isfinite(got[0][sel])), int(np.sum(~np.isfinite(got[0][sel])))
     e = metrics.mixed_err(got[0][sel] / 1e160, ref[sel] / 1e160, H)
     assert e.max() <= GATE, float(e.max())
+
+
+@pytest.mark.parametrize("n,B,cplx", [(7, 8192, False), (7, 2816, True), (8, 4096, False), (8, 2816, True),
+                                      (9, 1365, False), (9, 2048, False)])
+def test_mostly_shifted_batches_same_bits(apm, n, B, cplx):
+    """Batches that fill the chip and are shifted nearly throughout, whose parts go to the
+    wavefronts in groups of 3 or 9 (the corrections inside a group are its wavefront's): the bits
+    of the same eight matrices alone, whose parts go one by one."""
+    import torch
+    rng = np.random.default_rng(3700 + n)
+    A = _matrices(rng, 8, n, cplx, 12.0)
+    for b in (0, 1, 2, 4, 5, 7):
+        _zero_diagonal(A, b)
+    A[5] *= np.outer(np.exp2(rng.integers(-9, 9, 2 * n)), np.exp2(rng.integers(-9, 9, 2 * n)))
+    A[3, 3, 2] = np.nan
+    A[6, 2 * n - 1, 2 * n - 1] = 0.0
+    dA = torch.from_numpy(A).cuda()
+    want, info = apm.nand_minors(dA)
+    idx = torch.arange(B, device="cuda") % 8
+    out = torch.full((B, 3 ** n), 7.0, dtype=dA.dtype, device="cuda")
+    big, binfo = apm.nand_minors(dA[idx].contiguous(), out=out)
+    torch.cuda.synchronize()
+    assert info.tolist()[3] == -2 and all(info[b] > 0 for b in (0, 1, 2, 4, 5, 6, 7))
+    assert torch.equal(binfo, info[idx])
+    bits = (lambda t: torch.view_as_real(t).contiguous().view(torch.int64)) if cplx else (lambda t: t.view(torch.int64))
+    big, want = bits(big), bits(want)
+    for b in range(8):
+        assert torch.equal(big[b::8], want[b].expand_as(big[b::8])), (n, cplx, b)
