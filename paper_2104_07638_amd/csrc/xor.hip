@@ -1126,8 +1126,8 @@ hipError_t nand_parts_launch(const LaunchXor& L, hipStream_t st)
     } else {
         if (L.n != N) return nand_parts_launch<F, N + 1>(L, st);
         constexpr int kLevels = nand_levels(N);
-        // per CU: four wavefronts per SIMD (fp64); 11 by LDS, from 12 blocks on two per SIMD by registers
-        constexpr int64_t kWaves = kCus * (F::kComplex ? (N >= 12 ? 8 : 11) : 16);
+        // per CU: four wavefronts per SIMD (fp64); 11 by LDS, from 11 blocks on two per SIMD by registers
+        constexpr int64_t kWaves = kCus * (F::kComplex ? (N >= 11 ? 8 : 11) : 16);
         const int64_t parts = (int64_t)L.batch * pow3(kLevels);
         auto rounds = [&](int g) { return (parts / pow3(g) + kWaves - 1) / kWaves * pow3(g); };
         const int most = kLevels < 2 ? kLevels : 2;
