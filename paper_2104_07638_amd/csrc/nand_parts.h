@@ -46,8 +46,8 @@ constexpr int kSubLists = 64, kHeadStride = 32;
 constexpr int kHeadBad = kSubLists * kHeadStride, kHeadRedo2 = kHeadBad + 1, kHeadBad2 = kHeadBad + 2, kHeadGroup = kHeadBad + 3;
 constexpr int kRowParts = 12;              // parts of a wavefront of the register kernel
 
-// Wavefronts of the register kernel: four units of 3 T blocks each, three choices of the block
-// below them from 8 blocks on.
+// Wavefronts of the register kernel: one for four units (3^(N - 8) a matrix above 8 blocks) and,
+// from 8 blocks on, one of the three choices of the block below them.
 constexpr int64_t nand_row_waves(int N, int64_t batch)
 {
     int64_t units = batch;
